@@ -58,7 +58,6 @@ enum PlaneState { kEmpty = 0, kGridded = 1, kTransformed = 2 };
 struct Layout {
   int T;
   uint32_t chunk;
-  uint32_t chunk_degrid;
   int elem;
   int64_t ntiles;
   int64_t nkeys;
@@ -165,7 +164,29 @@ ws_status check_params(const ws_params* p) {
   return WS_OK;
 }
 
-ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L) {
+// Records one work item takes (automatic): the least power of two c in
+// [512, 4096] with c^2 >= max_vis.  An item is one workgroup, 512 run at
+// once, and the longest of them ends the launch: its time grows with c.  The
+// partial tiles of split tiles cost a write and a read each: their number
+// grows with max_vis / c.  Gridding and merge, us, at c = 512 / 1024 / 2048 /
+// 4096: 2e4 visibilities on 128^2 x 4 planes 29 / 33 / 44 / 67; 2e5 on
+// 512^2 x 8 FP64 74 / 84 / 100 / 125; 1e6 on 1024^2 x 16 215 / 163 / 169 /
+// 218; 1e7 on 4096^2 x 32 (2048, 4096) 1080 / 1000.
+uint32_t auto_chunk(int64_t max_vis) {
+  uint32_t c = 512;
+  while (c < 4096 && (int64_t)c * c < max_vis) c *= 2;
+  return c;
+}
+
+// Scratch slots for the partial tiles of split tiles, and the bytes of one.
+constexpr int64_t kMaxSlots = 4096;
+size_t partial_bytes(const Layout& L) {
+  return (size_t)L.T * L.T * 2 *
+         (L.elem == 16 ? sizeof(GridAcc<double>) : sizeof(GridAcc<float>));
+}
+
+ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
+                      int64_t max_slots = kMaxSlots) {
   ws_status st = check_params(p);
   if (st != WS_OK) return st;
   if (max_vis < 1 || max_vis > kMaxVis)
@@ -176,8 +197,7 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L) {
   if (L->T <= p->support - 1)
     return fail(WS_UNSUPPORTED_SIZE, "grid %d too small for support %d", nmin,
                 p->support);
-  L->chunk = p->chunk != 0 ? (uint32_t)p->chunk : 4096u;
-  L->chunk_degrid = p->chunk != 0 ? (uint32_t)p->chunk : 4096u;
+  L->chunk = p->chunk != 0 ? (uint32_t)p->chunk : auto_chunk(max_vis);
   L->elem = p->precision == WS_FP64 ? 16 : 8;
   const int64_t tu = p->nu / L->T, tv = p->nv / L->T;
   L->ntiles = tu * tv * p->nw;
@@ -206,12 +226,12 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L) {
     L->part_span = (uint32_t)span;
   }
   int64_t slots = 2 * max_vis / L->chunk + 64;
-  if (slots > 4096) slots = 4096;
+  if (slots > max_slots) slots = max_slots;
   L->max_slots = (uint32_t)slots;
   // Further work items beyond one per tile: at most max_slots when
   // gridding (split tiles hold scratch slots), at most max_vis / chunk when
   // degridding (each record is read by one tile).
-  const int64_t ex = max_vis / L->chunk_degrid + 2;
+  const int64_t ex = max_vis / L->chunk + 2;
   L->max_extra = (uint32_t)(ex > slots ? ex : slots);
   L->planes_bytes = (size_t)p->nw * p->nv * p->nu * L->elem;
   const size_t A = 256;
@@ -272,7 +292,8 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L) {
   // Column strips (T columns of one plane) that some gridding call since
   // the reset wrote records into.
   L->o_strips = take((size_t)p->nw * (p->nu / L->T) * 4);
-  L->o_partials = take((size_t)L->max_slots * L->T * L->T * L->elem);
+  // Partial tiles hold the gridder's FP64 sums on both paths.
+  L->o_partials = take(L->max_slots * partial_bytes(*L));
   // One plane of scratch for the natural-order output of ws_fft_planes
   // when columns use the four-step transform.
   L->o_scratch = take(p->nv > kOnePassCols
@@ -437,7 +458,8 @@ template <typename R>
 ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
                       int degrid, int64_t* n_dropped, uint32_t* max_items,
                       uint32_t* strips = nullptr, bool clear_strips = false,
-                      void* vis_out = nullptr, uint32_t* tslot = nullptr) {
+                      void* vis_out = nullptr, uint32_t* tslot = nullptr,
+                      uint32_t chunk_at_least = 0) {
   const Layout& L = pl->L;
   const Geo& g = pl->g;
   hipStream_t st = pl->stream;
@@ -448,7 +470,7 @@ ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
   uint32_t* slot = pl->w<uint32_t>(L.o_slot);
   uint32_t* counters = pl->w<uint32_t>(L.o_counters);
   uint32_t* split = pl->w<uint32_t>(L.o_split);
-  const uint32_t chunk = degrid ? L.chunk_degrid : L.chunk;
+  const uint32_t chunk = std::max(L.chunk, chunk_at_least);
   uint32_t* copies = pl->w<uint32_t>(L.o_copies);
   const uint32_t nkeys = (uint32_t)L.nkeys;
   const bool part = L.binning == WS_BINNING_PARTITION;
@@ -550,9 +572,8 @@ GridJob<R> make_job(ws_plan* pl, int accumulate, bool ts = false) {
   j.tile_slot = pl->w<uint32_t>(L.o_slot);
   j.rec = pl->w<Record<R>>(L.o_rec);
   j.desc = pl->w<uint32_t>(L.o_desc);
-  j.chunk = L.chunk;
   j.planes = static_cast<cplx<R>*>(pl->planes);
-  j.partials = pl->w<cplx<R>>(L.o_partials);
+  j.partials = pl->w<cplx<GridAcc<R>>>(L.o_partials);
   j.accumulate = accumulate;
   j.zero_idle = lazy_ok(pl) ? 0 : 1;
   j.tstore = ts ? pl->w<cplx<R>>(L.o_tstore) : nullptr;
@@ -746,7 +767,7 @@ ws_status degrid_impl(ws_plan* pl, const void* image, int image_is_real,
                            pl->w<uint2>(L.o_extra),
                            pl->w<uint32_t>(L.o_busy), pl->planes,
                            pl->work + L.o_rec,
-                           L.chunk_degrid, vis_out, max_items, pl->cus,
+                           L.chunk, vis_out, max_items, pl->cus,
                            pl->stream);
   }));
   return WS_OK;
@@ -886,6 +907,11 @@ ws_status batch_image_impl(ws_batch* b, const int64_t* m,
                            const double* const* uvw, const void* const* vis,
                            const float* const* weight, void* const* images) {
   uint32_t items = 0;
+  // The launch drains the items of all plans together: automatic chunks
+  // follow the batch's visibilities, not each plan's.
+  int64_t vis_total = 0;
+  for (int i = 0; i < b->n; ++i) vis_total += b->plans[i]->max_vis;
+  const uint32_t chunk = auto_chunk(vis_total);
   for (int i = 0; i < b->n; ++i) {
     ws_plan* pl = b->plans[i];
     pl->stream = b->stream;
@@ -897,7 +923,8 @@ ws_status batch_image_impl(ws_batch* b, const int64_t* m,
                           0, nullptr, &mi, pl->w<uint32_t>(pl->L.o_strips),
                           true, nullptr,
                           tstore_ok(pl) ? pl->w<uint32_t>(pl->L.o_tslot)
-                                        : nullptr));
+                                        : nullptr,
+                          pl->p.chunk != 0 ? 0u : chunk));
     items += mi;
   }
   ws_plan* p0 = b->plans[0];
@@ -1250,7 +1277,17 @@ ws_status ws_grid_image_noalloc(const ws_params* params, int64_t m,
   WS_TRY(make_layout(params, m > 0 ? m : 1, &L));
   const size_t planes_at = 0;
   const size_t work_at = align_up(L.planes_bytes, 256);
-  const size_t need = work_at + L.total;
+  size_t need = work_at + L.total;
+  if (need > kNoAllocBytes && L.max_slots > 1) {
+    // Partial-tile slots only spread split tiles over more workgroups: near
+    // the limit the problem keeps as many as fit.
+    const size_t over = need - kNoAllocBytes, pb = partial_bytes(L);
+    const size_t drop = (over + 255) / pb + 1;
+    WS_TRY(make_layout(params, m > 0 ? m : 1, &L,
+                       drop < L.max_slots ? (int64_t)(L.max_slots - drop)
+                                          : 1));
+    need = work_at + L.total;
+  }
   if (need > kNoAllocBytes)
     return fail(WS_WORKSPACE_TOO_SMALL,
                 "this problem needs %zu bytes of stack and workspace; the "

@@ -507,7 +507,8 @@ __device__ __forceinline__ void store_item(const GridJob<R>& j,
     store_tile_clear(s_re, s_im, j.pitch, T, j.g.cnorm, dst,
                      (size_t)j.g.nu, j.accumulate != 0);
   } else {
-    cplx<R>* part =
+    // Partial tiles keep the accumulators' precision: the merge rounds once.
+    cplx<GridAcc<R>>* part =
         j.partials + (size_t)(j.tile_slot[x.tile] + x.chunk) * T * T;
     store_tile_clear(s_re, s_im, j.pitch, T, 1.0, part, (size_t)T, false);
   }
@@ -646,51 +647,79 @@ __global__ __launch_bounds__(256) void k_zero_idle_batch(
   zero_idle_tile(jobs[p].g, jobs[p].idle, b, jobs[p].planes);
 }
 
+// Sums the partial tiles of split tiles in the accumulators' FP64 and rounds
+// each finished cell once.  A workgroup takes 1024 cells of a tile, eight
+// loads in flight each; what it waits on is the chain of sums over the tens
+// of chunks of the hottest tiles, so where a tile has more than
+// kMergeLong chunks it takes kMergeCells cells instead and cuts their lists
+// into kMergeRuns runs, whose sums are added in order (1e6 visibilities on
+// 1024^2 x 16 planes in chunks of 512: 82 -> 70 us; runs for every tile cost
+// the 4096^2 x 32 case 8 us of idle threads).  The grid is at most
+// kMergeTiles tiles wide and strides over the split list, whose length only
+// the device knows: one workgroup for every scratch slot spent 10 us on
+// those that found nothing to do.
+constexpr int kMergeCells = 256;
+constexpr int kMergeRuns = 4;
+constexpr uint32_t kMergeLong = 16;
+constexpr uint32_t kMergeTiles = 128;
+
 template <typename R>
-__global__ __launch_bounds__(1024) void k_grid_merge(
+__global__ __launch_bounds__(kMergeCells* kMergeRuns) void k_grid_merge(
     Geo g, const uint32_t* __restrict__ counters,
     const uint32_t* __restrict__ split_list,
     const uint32_t* __restrict__ tile_chunks,
     const uint32_t* __restrict__ tile_slot,
-    const cplx<R>* __restrict__ partials, cplx<R>* __restrict__ planes,
-    int accumulate, cplx<R>* __restrict__ tstore,
-    const uint32_t* __restrict__ tslot, uint32_t tcap) {
-  // Several workgroups per split tile (blockIdx.y), each summing the
-  // partials of its share of the cells in chunk order, eight loads in
-  // flight per thread: the hottest tiles have tens of chunks, and the
-  // chain of dependent sums per cell is what the merge waits on.
-  if (blockIdx.x >= counters[1]) return;
-  const int t = (int)split_list[blockIdx.x];
-  const uint32_t nch = tile_chunks[t];
-  const uint32_t slot = tile_slot[t];
+    const cplx<GridAcc<R>>* __restrict__ partials,
+    cplx<R>* __restrict__ planes, int accumulate,
+    cplx<R>* __restrict__ tstore, const uint32_t* __restrict__ tslot,
+    uint32_t tcap) {
+  using A = GridAcc<R>;
+  __shared__ cplx<A> s_sum[kMergeRuns][kMergeCells];
+  const uint32_t nsplit = counters[1];
   const int T = g.T;
-  int k, oy, ox;
-  tile_origin(g, t, k, oy, ox);
-  const uint32_t ts = tstore != nullptr ? tslot[t] : tcap;
-  const bool in_store = ts < tcap;
-  cplx<R>* dst = in_store ? tstore + (size_t)ts * T * T
-                          : planes + ((size_t)k * g.nv + oy) * g.nu + ox;
-  const R cn = (R)g.cnorm;
   const size_t tt = (size_t)T * T;
-  for (int i = blockIdx.y * blockDim.x + threadIdx.x; i < T * T;
-       i += gridDim.y * blockDim.x) {
-    const cplx<R>* src = partials + (size_t)slot * tt + i;
-    cplx<R> acc = {(R)0, (R)0};
-    uint32_t c = 0;
-    for (; c + 8 <= nch; c += 8) {
-      cplx<R> a[8];
+  for (uint32_t n = blockIdx.x; n < nsplit; n += gridDim.x) {
+    const int t = (int)split_list[n];
+    const uint32_t nch = tile_chunks[t];
+    const uint32_t runs = nch > kMergeLong ? kMergeRuns : 1u;
+    const int cells = kMergeCells * kMergeRuns / (int)runs;
+    const int cell = (int)threadIdx.x % cells;
+    const uint32_t run = threadIdx.x / cells;
+    const int i = (int)blockIdx.y * cells + cell;  // T^2 / 256 parts
+    const uint32_t per = (nch + runs - 1) / runs;
+    const uint32_t c1 = i < T * T ? min((run + 1) * per, nch) : 0u;
+    uint32_t c = min(run * per, c1);
+    const cplx<A>* src = partials + (size_t)tile_slot[t] * tt + i;
+    cplx<A> acc = {(A)0, (A)0};
+    for (; c + 8 <= c1; c += 8) {
+      cplx<A> a[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u) a[u] = src[(c + u) * tt];
 #pragma unroll
       for (int u = 0; u < 8; ++u) acc = cadd(acc, a[u]);
     }
-    for (; c < nch; ++c) acc = cadd(acc, src[c * tt]);
-    const int li = i % T, lj = i / T;
-    cplx<R> v = {cn * acc.re, cn * acc.im};
-    cplx<R>* p = in_store ? dst + tile_store_at<R>(T, lj, li)
-                          : dst + (size_t)lj * g.nu + li;
-    if (accumulate) v = cadd(*p, v);
-    *p = v;
+    for (; c < c1; ++c) acc = cadd(acc, src[c * tt]);
+    if (runs > 1) {
+      s_sum[run][cell] = acc;
+      __syncthreads();
+      if (run == 0) {
+#pragma unroll
+        for (int u = 1; u < kMergeRuns; ++u) acc = cadd(acc, s_sum[u][cell]);
+      }
+      __syncthreads();  // read before the next tile's sums
+    }
+    if (run == 0 && i < T * T) {
+      int k, oy, ox;
+      tile_origin(g, t, k, oy, ox);
+      const uint32_t ts = tstore != nullptr ? tslot[t] : tcap;
+      const int li = i % T, lj = i / T;
+      cplx<R> v = {(R)(g.cnorm * acc.re), (R)(g.cnorm * acc.im)};
+      cplx<R>* p =
+          ts < tcap ? tstore + (size_t)ts * tt + tile_store_at<R>(T, lj, li)
+                    : planes + ((size_t)k * g.nv + oy + lj) * g.nu + ox + li;
+      if (accumulate) v = cadd(*p, v);
+      *p = v;
+    }
   }
 }
 
@@ -936,11 +965,13 @@ void launch_grid_merge(const Geo& g, const uint32_t* counters,
                        void* planes, int accumulate, uint32_t max_split,
                        void* tstore, const uint32_t* tslot, uint32_t tcap,
                        hipStream_t st) {
-  constexpr unsigned kMergeParts = 4;
-  hipLaunchKernelGGL(k_grid_merge<R>, dim3(max_split, kMergeParts), dim3(1024),
-                     0, st, g,
-                     counters, split_list, tile_chunks, tile_slot,
-                     (const cplx<R>*)partials, (cplx<R>*)planes, accumulate,
+  hipLaunchKernelGGL(k_grid_merge<R>,
+                     dim3(max_split < kMergeTiles ? max_split : kMergeTiles,
+                          (unsigned)(g.T * g.T / kMergeCells)),
+                     dim3(kMergeCells * kMergeRuns), 0, st, g, counters,
+                     split_list, tile_chunks, tile_slot,
+                     (const cplx<GridAcc<R>>*)partials, (cplx<R>*)planes,
+                     accumulate,
                      (cplx<R>*)tstore, tslot, tcap);
 }
 

@@ -139,9 +139,8 @@ struct GridJob {
   const uint32_t* tile_slot;
   const Record<R>* rec;
   const uint32_t* desc;       // item descriptors (kDescWords words each)
-  uint32_t chunk;
   cplx<R>* planes;
-  cplx<R>* partials;
+  cplx<GridAcc<R>>* partials;  // tiles of split items, unrounded
   int accumulate;
   int zero_idle;              // batch: this job's idle tiles need zeros
   // Busy-tile store (one-call path of 4096-row FP32 stacks): finished
