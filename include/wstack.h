@@ -113,8 +113,10 @@ typedef int32_t ws_status;
  *            tile rows), then by (tile column, region), with per-workgroup
  *            histograms and no global atomics; WS_BINNING_HASHED - one
  *            counting sort with LDS-hashed counts and global atomics;
- *            WS_BINNING_AUTO - the partition whenever its histograms fit
- *            (at most 16384 buckets of at most 16384 keys), else hashed.
+ *            WS_BINNING_AUTO - for at most 16384 keys in all and 2^20
+ *            visibilities one level of the partition (a histogram of every
+ *            key); otherwise the partition whenever its histograms fit (at
+ *            most 16384 buckets of at most 16384 keys), else hashed.
  *            Requesting WS_BINNING_PARTITION where it does not fit is
  *            WS_UNSUPPORTED_SIZE. */
 #define WS_BINNING_AUTO 0

@@ -64,8 +64,10 @@ struct Layout {
   uint32_t max_slots;
   uint32_t max_extra;
   size_t planes_bytes;
-  // binning: WS_BINNING_PARTITION or WS_BINNING_HASHED (resolved)
+  // binning: WS_BINNING_PARTITION or WS_BINNING_HASHED (resolved), or the
+  // direct sort that automatic plans small enough take
   int binning;
+  bool direct;
   uint32_t part_buckets, part_span;  // partition: buckets and keys each
   // Busy-tile store of the one-call path (FP32, 4096-row columns, tile
   // edge 64, fused rows): tiles with records are gridded into slots of
@@ -224,6 +226,7 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
                      ? WS_BINNING_HASHED : WS_BINNING_PARTITION;
     L->part_buckets = (uint32_t)buckets;
     L->part_span = (uint32_t)span;
+    L->direct = p->binning == WS_BINNING_AUTO && direct_fits(max_vis, L->nkeys);
   }
   int64_t slots = 2 * max_vis / L->chunk + 64;
   if (slots > max_slots) slots = max_slots;
@@ -248,17 +251,21 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
   L->o_corr = take((size_t)(p->nu + p->nv) * 8);
   // Key counts, scanned in place into key offsets (+ the total).
   L->o_counts = take((size_t)(L->nkeys + 1) * 4);
-  const bool part = L->binning == WS_BINNING_PARTITION;
+  const bool part = L->binning == WS_BINNING_PARTITION && !L->direct;
   // kCountCopies copies of the key counts, turned into per-copy offsets
   // (hashed binning only).
-  L->o_copies = take(part ? 0 : (size_t)kCountCopies * L->nkeys * 4);
+  L->o_copies = take(part || L->direct ? 0
+                                     : (size_t)kCountCopies * L->nkeys * 4);
   const int64_t pblocks = partition_blocks(max_vis, L->elem);
   const int64_t pscan = (int64_t)L->part_buckets * pblocks;
   L->o_sums = take((size_t)(scan_sums_len(nscan) + 1) * 4);
   // Partition: level-1 histograms (block-major, then bucket-major and
   // scanned), records and keys in bucket order, chunk starts, level-2
   // ranks and histograms.
-  L->o_p_hist1 = take(part ? (size_t)pscan * 4 : 0);
+  L->o_p_hist1 =
+      take(L->direct ? (size_t)direct_hist_words(max_vis, L->nkeys) * 4
+           : part    ? (size_t)pscan * 4
+                     : 0);
   L->o_p_hist1x = take(part ? (size_t)pscan * 4 : 0);
   L->o_p_btot = take(part ? (size_t)pblocks * 4 : 0);
   L->o_p_bounds = take(part ? (size_t)(L->part_buckets + 1) * 4 : 0);
@@ -474,12 +481,45 @@ ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
   uint32_t* copies = pl->w<uint32_t>(L.o_copies);
   const uint32_t nkeys = (uint32_t)L.nkeys;
   const bool part = L.binning == WS_BINNING_PARTITION;
-  WS_TRY(launch(pl, "zero_counts", [&] {
-    if (!part) launch_zero_u32(copies, kCountCopies * L.nkeys, st);
-    launch_zero_u32(counters, 16, st);
-    if (strips != nullptr && clear_strips)
-      launch_zero_u32(strips, (int64_t)g.nw * g.tiles_u, st);
-  }));
+  auto* drop = reinterpret_cast<unsigned long long*>(n_dropped);
+  BinClear clear{};
+  clear.counters = counters;
+  if (strips != nullptr && clear_strips) {
+    clear.strips = strips;
+    clear.nstrips = (uint32_t)(g.nw * g.tiles_u);
+  }
+  TileWork tw{};
+  tw.degrid = degrid;
+  tw.chunk = chunk;
+  tw.max_slots = L.max_slots;
+  tw.max_extra = L.max_extra;
+  tw.tile_chunks = chunks;
+  tw.tile_slot = slot;
+  tw.counters = counters;
+  tw.split_list = split;
+  tw.extra = pl->w<uint2>(L.o_extra);
+  tw.busy = pl->w<uint32_t>(L.o_busy);
+  tw.idle = pl->w<uint32_t>(L.o_idle);
+  tw.strips = strips;
+  tw.tslot = tslot;
+  tw.desc = pl->w<uint32_t>(L.o_desc);
+  // Items: one per tile plus the further chunks of split tiles.
+  const int64_t reads = degrid ? m : 4 * m;
+  int64_t extra = (reads + chunk - 1) / chunk + 1;
+  if (extra > L.max_extra) extra = L.max_extra;
+  *max_items = (uint32_t)(L.ntiles + extra);
+  if (L.direct) {
+    DirectWork w;
+    w.nkeys = nkeys;
+    w.keyrank = keyrank;
+    w.hist = pl->w<uint32_t>(L.o_p_hist1);
+    w.offsets = counts;
+    w.rec = pl->work + L.o_rec;
+    return launch(pl, "direct_sort", [&] {
+      launch_direct_sort<R>(g, src, m, pl->max_vis, w, tw, clear, drop,
+                            vis_out, st);
+    });
+  }
   if (part) {
     PartWork w;
     w.nbuckets = L.part_buckets;
@@ -499,7 +539,7 @@ ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
     w.hist2 = pl->w<uint32_t>(L.o_p_hist2);
     w.offsets = counts;
     w.rec = pl->work + L.o_rec;
-    auto* drop = reinterpret_cast<unsigned long long*>(n_dropped);
+    w.clear = clear;
     WS_TRY(launch(pl, "part_count1", [&] {
       launch_part_count1<R>(g, src, m, w, drop, st);
     }));
@@ -515,9 +555,13 @@ ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
       launch_part_scatter2<R>(m, w, st);
     }));
   } else {
+    WS_TRY(launch(pl, "zero_counts", [&] {
+      launch_zero_u32(copies, kCountCopies * L.nkeys, st);
+      launch_zero_u32(counters, 16, st);
+      launch_zero_u32(clear.strips, (int64_t)clear.nstrips, st);
+    }));
     WS_TRY(launch(pl, "bin_count", [&] {
-      launch_bin_count(g, src, m, copies, nkeys, keyrank,
-                       reinterpret_cast<unsigned long long*>(n_dropped), st);
+      launch_bin_count(g, src, m, copies, nkeys, keyrank, drop, st);
     }));
     WS_TRY(launch(pl, "scan_keys", [&] {
       launch_fold_copies(copies, nkeys, counts, st);
@@ -529,27 +573,8 @@ ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
                             pl->work + L.o_rec, degrid, vis_out, st);
     }));
   }
-  WS_TRY(launch(pl, "tile_work", [&] {
-    launch_tile_work(g, counts, degrid, chunk, chunks, slot, counters, split,
-                     L.max_slots, pl->w<uint2>(L.o_extra), L.max_extra,
-                     pl->w<uint32_t>(L.o_busy), pl->w<uint32_t>(L.o_idle),
-                     strips, tslot, st);
-  }));
-  // Items: one per tile plus the further chunks of split tiles.
-  const int64_t reads = degrid ? m : 4 * m;
-  int64_t extra = (reads + chunk - 1) / chunk + 1;
-  if (extra > L.max_extra) extra = L.max_extra;
-  *max_items = (uint32_t)(L.ntiles + extra);
-  if (!degrid) {
-    // Extra items are capped by max_extra, so every item has a slot.
-    WS_TRY(launch(pl, "item_desc", [&] {
-      launch_item_desc(g, counts, counters, pl->w<uint2>(L.o_extra),
-                       pl->w<uint32_t>(L.o_busy), chunks, chunk,
-                       pl->w<uint32_t>(L.o_desc),
-                       (uint32_t)(L.ntiles + L.max_extra), st);
-    }));
-  }
-  return WS_OK;
+  return launch(pl, "tile_work",
+                [&] { launch_tile_work(g, counts, tw, st); });
 }
 
 bool lazy_ok(const ws_plan* pl);
@@ -1008,24 +1033,16 @@ ws_status init_plan(ws_plan* pl, const ws_params* params, int64_t max_vis,
       pl->cus = n;
   }
   pl->profile = false;
-  WS_TRY(launch(pl, "zero_line", [&] {
-    launch_zero_u32(pl->w<uint32_t>(L.o_zero), 64, pl->stream);
-  }));
-  if (params->correct) {
-    double* corr = pl->w<double>(L.o_corr);
-    pl->g.corr = corr;
-    WS_TRY(launch(pl, "correction",
-                  [&] { launch_correction(pl->g, corr, pl->stream); }));
-  }
-  if (params->precision == WS_FP64) {
-    return launch(pl, "twiddles", [&] {
-      launch_twiddles<double>(pl->work + L.o_tw_u, params->nu, pl->stream);
-      launch_twiddles<double>(pl->work + L.o_tw_v, params->nv, pl->stream);
-    });
-  }
-  return launch(pl, "twiddles", [&] {
-    launch_twiddles<float>(pl->work + L.o_tw_u, params->nu, pl->stream);
-    launch_twiddles<float>(pl->work + L.o_tw_v, params->nv, pl->stream);
+  if (params->correct) pl->g.corr = pl->w<double>(L.o_corr);
+  return launch(pl, "tables", [&] {
+    if (params->precision == WS_FP64)
+      launch_tables<double>(pl->g, pl->work + L.o_tw_u, pl->work + L.o_tw_v,
+                            pl->w<double>(L.o_corr),
+                            pl->w<uint32_t>(L.o_zero), pl->stream);
+    else
+      launch_tables<float>(pl->g, pl->work + L.o_tw_u, pl->work + L.o_tw_v,
+                           pl->w<double>(L.o_corr), pl->w<uint32_t>(L.o_zero),
+                           pl->stream);
   });
 }
 

@@ -296,6 +296,32 @@ __global__ __launch_bounds__(kScanThreads) void k_scan_apply(
   if (blockIdx.x == 0 && threadIdx.x == 0) out[n] = sums[nb];
 }
 
+// The record of visibility gi (one that place() accepts).
+template <typename R>
+__device__ __forceinline__ Record<R> make_record(const Geo& g,
+                                                 const VisSource& src,
+                                                 int64_t gi, int degrid) {
+  double x, y, u, v, w;
+  int i0, j0, k;
+  source_uvw(src, gi, u, v, w);
+  place(g, u, v, w, x, y, i0, j0, k);
+  Record<R> r;
+  // Fractional offsets from the nearest cell, subtracted in FP64 first.
+  r.dx = (R)(x - (double)i0);
+  r.dy = (R)(y - (double)j0);
+  if (!degrid) {
+    const cplx<R> vv = source_value<R>(src, gi);
+    r.vr = vv.re;
+    r.vi = vv.im;
+  } else {
+    r.vr = (R)source_weight(src, gi);
+    r.vi = (R)0;
+  }
+  r.cell = pack_cell(i0, j0);
+  r.idx = (uint32_t)gi;
+  return r;
+}
+
 template <typename R>
 __global__ __launch_bounds__(256) void k_bin_scatter(
     Geo g, VisSource src, int64_t m,
@@ -311,28 +337,10 @@ __global__ __launch_bounds__(256) void k_bin_scatter(
     if (degrid) vis_out[gi] = cplx<R>{(R)0, (R)0};
     return;
   }
-  double x, y, u, v, w;
-  int i0, j0, k;
-  source_uvw(src, gi, u, v, w);
-  place(g, u, v, w, x, y, i0, j0, k);
   // The copy the counting workgroup of this visibility added into.
   const int64_t copy = (gi / kCountPerBlock) % kCountCopies;
   const uint32_t pos = offsets[copy * nkeys + kr.x] + kr.y;
-  Record<R> r;
-  // Fractional offsets from the nearest cell, subtracted in FP64 first.
-  r.dx = (R)(x - (double)i0);
-  r.dy = (R)(y - (double)j0);
-  if (!degrid) {
-    const cplx<R> vv = source_value<R>(src, gi);
-    r.vr = vv.re;
-    r.vi = vv.im;
-  } else {
-    r.vr = (R)source_weight(src, gi);
-    r.vi = (R)0;
-  }
-  r.cell = pack_cell(i0, j0);
-  r.idx = (uint32_t)gi;
-  rec[pos] = r;
+  rec[pos] = make_record<R>(g, src, gi, degrid);
 }
 
 // Appends to a list with one atomic per wavefront: returns this lane's slot
@@ -349,32 +357,124 @@ __device__ __forceinline__ uint32_t wave_append(uint32_t* counter, bool pred) {
   return base + (uint32_t)__popcll(below);
 }
 
+// Records of tile t: its own (degridding), or those of its ten key ranges
+// (gridding), whose first records and lengths stay in registers for the
+// descriptors.  `off` is the key offset table.
+struct TileRecords {
+  uint32_t work;
+  uint32_t first[kSegments], len[kSegments];
+};
+
+template <class Off>
+__device__ __forceinline__ TileRecords tile_records(const Geo& g, int t,
+                                                    int mode_degrid, Off off) {
+  TileRecords r;
+  r.work = 0;
+  if (mode_degrid) {
+    r.work = off[(uint32_t)t * kRegions + kRegions] -
+             off[(uint32_t)t * kRegions];
+    return r;
+  }
+  uint32_t lo[kSegments], hi[kSegments];
+  tile_segments(g, t, lo, hi);
+#pragma unroll
+  for (int s = 0; s < kSegments; ++s) {
+    r.first[s] = off[lo[s]];
+    r.len[s] = off[hi[s]] - r.first[s];
+    r.work += r.len[s];
+  }
+  return r;
+}
+
+// Cuts tile t into work items and writes everything later passes read about
+// it: its chunk count (0 marks a tile without records, whose stack cells may
+// be left unwritten by a fused grid-and-image call), its entry `at` in the
+// busy or idle list, its column strip's mark, the scratch slots of a split
+// tile, and (gridding) one descriptor per item.  ctr: [0] scratch slots
+// taken, [1] split tiles, [2] extra items; in LDS or in device memory.
+__device__ __forceinline__ void emit_tile(const Geo& g, const TileWork& w,
+                                          int t, const TileRecords& r,
+                                          uint32_t at, uint32_t* ctr) {
+  if (r.work == 0) {
+    w.idle[at] = (uint32_t)t;
+    w.tile_slot[t] = 0;
+    w.tile_chunks[t] = 0u;
+    return;
+  }
+  w.busy[at] = (uint32_t)t;
+  if (w.tslot != nullptr) w.tslot[t] = at;  // its slot in the busy-tile store
+  if (w.strips != nullptr) {
+    // Column strip of this tile: plane k, tile column tx.
+    const int per_plane = g.tiles_u * g.tiles_v;
+    const int k = t / per_plane;
+    const int tx = (t - k * per_plane) % g.tiles_u;
+    w.strips[k * g.tiles_u + tx] = 1u;
+  }
+  uint32_t nch = (r.work + w.chunk - 1) / w.chunk;
+  uint32_t slot = 0;
+  if (nch > 1 && !w.degrid) {
+    const uint32_t s0 = atomicAdd(&ctr[0], nch);
+    if (s0 + nch <= w.max_slots) {
+      slot = s0;
+      w.split_list[atomicAdd(&ctr[1], 1u)] = (uint32_t)t;
+    } else {
+      nch = 1;  // scratch exhausted: one item grids the whole tile
+    }
+  }
+  uint32_t e0 = 0;
+  if (nch > 1) {
+    e0 = atomicAdd(&ctr[2], nch - 1);
+    if (e0 + (nch - 1) > w.max_extra)
+      nch = 1;  // cannot happen with the sizes the plan reserves
+  }
+  w.tile_slot[t] = slot;
+  w.tile_chunks[t] = nch;
+  if (w.degrid) {
+    for (uint32_t c = 1; c < nch; ++c)
+      w.extra[e0 + c - 1] = make_uint2((uint32_t)t, c);
+    return;
+  }
+  // Descriptors (layout: kDescWords in ws_kernels.h).
+  uint32_t d[kDescWords];
+  uint32_t cum = 0, prev = 0;
+#pragma unroll
+  for (int s = 0; s < kSegments; ++s) {
+    const uint32_t off = r.first[s] - cum;
+    if (s == 0) {
+      d[5] = off;
+    } else {
+      d[5 + s] = cum;
+      d[5 + kSegments - 1 + s] = off - prev;
+    }
+    prev = off;
+    cum += r.len[s];
+  }
+  d[0] = (uint32_t)t;
+  d[1] = nch;
+  for (uint32_t c = 0; c < nch; ++c) {
+    d[2] = nch == 1 ? at : c;
+    d[3] = c * w.chunk;
+    d[4] = nch == 1 ? cum : min(cum, (c + 1) * w.chunk);
+    const size_t n = c == 0 ? (size_t)at : (size_t)g.ntiles + e0 + c - 1;
+    uint4* p = reinterpret_cast<uint4*>(w.desc + n * kDescWords);
+#pragma unroll
+    for (int q = 0; q < kDescWords / 4; ++q)
+      p[q] = make_uint4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
+  }
+}
+
 __global__ __launch_bounds__(256) void k_tile_work(
-    Geo g, const uint32_t* __restrict__ offsets, int mode_degrid,
-    uint32_t chunk, uint32_t* __restrict__ tile_chunks,
-    uint32_t* __restrict__ tile_slot, uint32_t* __restrict__ counters,
-    uint32_t* __restrict__ split_list, uint32_t max_slots,
-    uint2* __restrict__ extra, uint32_t max_extra,
-    uint32_t* __restrict__ busy, uint32_t* __restrict__ idle,
-    uint32_t* __restrict__ strips, uint32_t* __restrict__ tslot) {
+    Geo g, const uint32_t* __restrict__ offsets, TileWork w) {
   // counters[0]: scratch slots taken, [1]: split tiles, [2]: extra items,
   // [4]: tiles with records (listed in busy), [5]: tiles without (idle),
   // [6..7]: 64-bit sum of the records every tile reads.
+  uint32_t* counters = w.counters;
   const int t = blockIdx.x * blockDim.x + threadIdx.x;
   const bool live = t < g.ntiles;
-  uint32_t work = 0;
-  if (live) {
-    if (mode_degrid) {
-      work = offsets[(uint32_t)t * kRegions + kRegions] -
-             offsets[(uint32_t)t * kRegions];
-    } else {
-      uint32_t lo[kSegments], hi[kSegments];
-      tile_segments(g, t, lo, hi);
-#pragma unroll
-      for (int s = 0; s < kSegments; ++s)
-        work += offsets[hi[s]] - offsets[lo[s]];
-    }
-  }
+  TileRecords r;
+  r.work = 0;
+  if (live) r = tile_records(g, t, w.degrid, offsets);
+  const uint32_t work = r.work;
   // Busy tiles are listed per wavefront (the gridder takes items in list
   // order, and wavefront-sized runs of neighbouring tiles measured best);
   // idle tiles and the total record reads (diagnostics) need no order and
@@ -406,45 +506,9 @@ __global__ __launch_bounds__(256) void k_tile_work(
   }
   __syncthreads();
   uint32_t ii = s_base;
-  for (int w = 0; w < wave; ++w) ii += s_idle[w];
+  for (int q = 0; q < wave; ++q) ii += s_idle[q];
   ii += (uint32_t)__popcll(imask & ((1ull << lane) - 1ull));
-  if (!live) return;
-  if (work > 0) {
-    busy[ib] = (uint32_t)t;
-    if (tslot != nullptr) tslot[t] = ib;  // its slot in the busy-tile store
-  } else {
-    idle[ii] = (uint32_t)t;
-  }
-  if (work > 0 && strips != nullptr) {
-    // Column strip of this tile: plane k, tile column tx.
-    const int per_plane = g.tiles_u * g.tiles_v;
-    const int k = t / per_plane;
-    const int tx = (t - k * per_plane) % g.tiles_u;
-    strips[k * g.tiles_u + tx] = 1u;
-  }
-  uint32_t nch = work == 0 ? 1u : (work + chunk - 1) / chunk;
-  tile_slot[t] = 0;
-  if (nch > 1 && !mode_degrid) {
-    const uint32_t s0 = atomicAdd(&counters[0], nch);
-    if (s0 + nch <= max_slots) {
-      tile_slot[t] = s0;
-      split_list[atomicAdd(&counters[1], 1u)] = (uint32_t)t;
-    } else {
-      nch = 1;  // scratch exhausted: one item grids the whole tile
-    }
-  }
-  if (nch > 1) {
-    const uint32_t e0 = atomicAdd(&counters[2], nch - 1);
-    if (e0 + (nch - 1) <= max_extra) {
-      for (uint32_t c = 1; c < nch; ++c)
-        extra[e0 + c - 1] = make_uint2((uint32_t)t, c);
-    } else {
-      nch = 1;  // cannot happen with the sizes the plan reserves
-    }
-  }
-  // 0 marks a tile without records (its stack cells may be left unwritten
-  // by a fused grid-and-image call).
-  tile_chunks[t] = work == 0 ? 0u : nch;
+  if (live) emit_tile(g, w, t, r, work > 0 ? ib : ii, counters);
 }
 
 // ---- two-level partition (no global atomics) ------------------------------
@@ -481,6 +545,14 @@ __global__ __launch_bounds__(256) void k_tile_work(
 // visibilities: as many records as fit the LDS staging area.
 
 constexpr int kPartThreads = 1024;
+// Limits of the direct sort: keys (LDS words of its histogram), and
+// visibilities (beyond, its scattered record writes cost more than the
+// partition's second level).  The key totals come from one workgroup up to
+// kDirectCols histogram words (twelve rounds of loads), else from a kernel
+// of their own.
+constexpr int64_t kDirectKeys = 16384;
+constexpr int64_t kDirectVis = 1 << 20;
+constexpr uint64_t kDirectCols = 65536;
 constexpr int kPartSegs = 64;  // block segments of the level-1 scan
 
 // In-place exclusive scan of n LDS counters (each thread a contiguous run);
@@ -646,25 +718,8 @@ __global__ __launch_bounds__(kPartThreads) void k_part_scatter1(
       if (degrid) vis_out[gi] = cplx<R>{(R)0, (R)0};
       continue;
     }
-    double x, y, u, v, w;
-    int i0, j0, k;
-    source_uvw(src, gi, u, v, w);
-    place(g, u, v, w, x, y, i0, j0, k);
-    Record<R> r;
-    r.dx = (R)(x - (double)i0);
-    r.dy = (R)(y - (double)j0);
-    if (!degrid) {
-      const cplx<R> vv = source_value<R>(src, gi);
-      r.vr = vv.re;
-      r.vi = vv.im;
-    } else {
-      r.vr = (R)source_weight(src, gi);
-      r.vi = (R)0;
-    }
-    r.cell = pack_cell(i0, j0);
-    r.idx = (uint32_t)gi;
     const uint32_t slot = ex[kr.x / span] + kr.y;
-    s_rec[slot] = r;
+    s_rec[slot] = make_record<R>(g, src, gi, degrid);
     s_key[slot] = kr.x;  // for the write-out and level 2
   }
   __syncthreads();
@@ -678,14 +733,23 @@ __global__ __launch_bounds__(kPartThreads) void k_part_scatter1(
   }
 }
 
+// Zeros of the tile work counters and (where asked for) of the strip marks:
+// one workgroup of a kernel that runs before the tile work pass.
+__device__ __forceinline__ void bin_clear(const BinClear& c) {
+  for (uint32_t i = threadIdx.x; i < 16u; i += blockDim.x) c.counters[i] = 0u;
+  for (uint32_t i = threadIdx.x; i < c.nstrips; i += blockDim.x)
+    c.strips[i] = 0u;
+}
+
 // One workgroup: bucket totals (in bounds[], from col_seg) -> bucket bounds
 // (exclusive scan, bounds[nbuckets] = total), then chunks per bucket ->
 // first chunk of every bucket (chunk0[nbuckets] = total chunks).  Each
 // thread takes a contiguous run of buckets (nbuckets <= 16384).
 __global__ __launch_bounds__(kPartThreads) void k_part_bounds(
     uint32_t* __restrict__ bounds, uint32_t nbuckets, uint32_t chunk,
-    uint32_t* __restrict__ chunk0) {
+    uint32_t* __restrict__ chunk0, BinClear clear) {
   __shared__ uint32_t s_tmp[kPartThreads / 64];
+  bin_clear(clear);
   const uint32_t per = (nbuckets + kPartThreads - 1) / kPartThreads;
   const uint32_t c0 = threadIdx.x * per;
   const uint32_t c1 = min(c0 + per, nbuckets);
@@ -712,6 +776,101 @@ __global__ __launch_bounds__(kPartThreads) void k_part_bounds(
   if (threadIdx.x == 0) {
     bounds[nbuckets] = total;
     chunk0[nbuckets] = ntotal;
+  }
+}
+
+// The whole level-1 scan (col_sum, col_seg, part_bounds, col_apply) in one
+// workgroup, for histograms of at most kSmallScan words: four launches of a
+// few microseconds each become one (28 -> 13 us for 244 workgroups of 256
+// buckets).  Thread (segment, bucket) sums its run of blocks eight loads at
+// a time; more than 1024 buckets take one segment and several turns.
+constexpr uint32_t kSmallScan = 65536;
+
+__global__ __launch_bounds__(kPartThreads) void k_part_scan1_small(
+    uint32_t* __restrict__ hist, uint32_t nb, uint32_t nc, uint32_t chunk,
+    uint32_t* __restrict__ bounds, uint32_t* __restrict__ chunk0,
+    BinClear clear) {
+  extern __shared__ uint32_t s_bkt[];  // nc words, then kPartThreads
+  uint32_t* s_seg = s_bkt + nc;
+  __shared__ uint32_t s_tmp[kPartThreads / 64];
+  bin_clear(clear);
+  const uint32_t nseg = nc >= kPartThreads ? 1u : kPartThreads / nc;
+  const uint32_t seg = threadIdx.x / nc, c0 = threadIdx.x % nc;
+  const bool on = nc >= kPartThreads || seg < nseg;
+  const uint32_t first = nc >= kPartThreads ? threadIdx.x : c0;
+  const uint32_t step = nc >= kPartThreads ? (uint32_t)kPartThreads : nc;
+  const uint32_t sg = nc >= kPartThreads ? 0u : seg;
+  const uint32_t seglen = (nb + nseg - 1) / nseg;
+  const uint32_t b0 = min(sg * seglen, nb), b1 = min(b0 + seglen, nb);
+  auto column = [&](uint32_t c) {
+    uint32_t acc = 0, b = b0;
+    for (; b + 8 <= b1; b += 8) {
+      uint32_t v[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) v[u] = hist[(size_t)(b + u) * nc + c];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) acc += v[u];
+    }
+    for (; b < b1; ++b) acc += hist[(size_t)b * nc + c];
+    return acc;
+  };
+  if (on) {
+    for (uint32_t c = first; c < nc; c += step) {
+      const uint32_t v = column(c);
+      if (nseg > 1) s_seg[sg * nc + c] = v;
+      else s_bkt[c] = v;
+    }
+  }
+  __syncthreads();
+  if (nseg > 1 && threadIdx.x < nc) {
+    uint32_t run = 0;
+    for (uint32_t q = 0; q < nseg; ++q) {
+      const uint32_t v = s_seg[q * nc + threadIdx.x];
+      s_seg[q * nc + threadIdx.x] = run;
+      run += v;
+    }
+    s_bkt[threadIdx.x] = run;
+  }
+  __syncthreads();
+  // Level-2 chunks, then bucket bounds, both exclusive scans over buckets.
+  const uint32_t per = (nc + kPartThreads - 1) / kPartThreads;
+  const uint32_t k0 = min(threadIdx.x * per, nc), k1 = min(k0 + per, nc);
+  uint32_t nch = 0;
+  for (uint32_t c = k0; c < k1; ++c) nch += (s_bkt[c] + chunk - 1) / chunk;
+  uint32_t ntotal;
+  uint32_t crun = block_exclusive_scan(nch, s_tmp, &ntotal);
+  for (uint32_t c = k0; c < k1; ++c) {
+    chunk0[c] = crun;
+    crun += (s_bkt[c] + chunk - 1) / chunk;
+  }
+  const uint32_t total = lds_exclusive_scan(s_bkt, nc, s_tmp);
+  for (uint32_t c = threadIdx.x; c < nc; c += kPartThreads)
+    bounds[c] = s_bkt[c];
+  if (threadIdx.x == 0) {
+    bounds[nc] = total;
+    chunk0[nc] = ntotal;
+  }
+  if (on) {
+    for (uint32_t c = first; c < nc; c += step) {
+      uint32_t run = s_bkt[c] + (nseg > 1 ? s_seg[sg * nc + c] : 0u);
+      uint32_t b = b0;
+      for (; b + 8 <= b1; b += 8) {
+        uint32_t v[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) v[u] = hist[(size_t)(b + u) * nc + c];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          hist[(size_t)(b + u) * nc + c] = run;
+          run += v[u];
+        }
+      }
+      for (; b < b1; ++b) {
+        uint32_t* p = hist + (size_t)b * nc + c;
+        const uint32_t v = *p;
+        *p = run;
+        run += v;
+      }
+    }
   }
 }
 
@@ -832,6 +991,152 @@ __global__ __launch_bounds__(kPartThreads) void k_part_scatter2(
   }
 }
 
+// ---- direct sort (small plans) --------------------------------------------
+//
+// Where all keys of a plan fit one dense LDS histogram (kDirectKeys) the
+// partition needs no second level, and its single-workgroup scans no launches
+// of their own.  Small calls are bound by the number of launches (~4 us
+// each): this sort and the tile work take three or four of them, the
+// partition and its tile work ten.
+//
+//   direct_count    placement, key and rank within the workgroup's key (LDS
+//                   atomic); the workgroup's key histogram, block-major
+//   direct_cols     histograms -> running sums over the blocks, key totals
+//                   (only where direct_tiles would be slow to do it itself)
+//   direct_tiles    one workgroup: key offsets, then the tile work pass
+//   direct_scatter  records to offset[key] + sum of earlier blocks + rank
+
+template <int V>
+__global__ __launch_bounds__(kPartThreads) void k_direct_count(
+    Geo g, VisSource src, int64_t m, uint32_t nkeys,
+    uint2* __restrict__ keyrank, uint32_t* __restrict__ hist,
+    unsigned long long* __restrict__ dropped) {
+  constexpr int PER = V / kPartThreads;
+  extern __shared__ uint32_t s_h[];  // nkeys counters
+  __shared__ unsigned long long s_drop;
+  const int tid = threadIdx.x;
+  const int64_t base = (int64_t)blockIdx.x * V;
+  double cu[PER], cv[PER], cw[PER];
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    int64_t gi = base + (int64_t)e * kPartThreads + tid;
+    gi = gi < m ? gi : m - 1;
+    source_uvw(src, gi, cu[e], cv[e], cw[e]);
+  }
+  for (uint32_t c = tid; c < nkeys; c += kPartThreads) s_h[c] = 0u;
+  if (tid == 0) s_drop = 0;
+  __syncthreads();
+  unsigned long long my_drop = 0;
+#pragma unroll
+  for (int e = 0; e < PER; ++e) {
+    const int64_t gi = base + (int64_t)e * kPartThreads + tid;
+    if (gi >= m) continue;
+    double x, y;
+    int i0, j0, k;
+    uint2 kr = make_uint2(kNoKey, 0u);
+    if (place(g, cu[e], cv[e], cw[e], x, y, i0, j0, k)) {
+      my_drop += (unsigned long long)(g.K * g.K - taps_on_grid(g, i0, j0));
+      kr.x = bin_key(g, i0, j0, k);
+      kr.y = atomicAdd(&s_h[kr.x], 1u);
+    } else {
+      my_drop += (unsigned long long)(g.K * g.K);
+    }
+    keyrank[gi] = kr;
+  }
+  if (dropped != nullptr && my_drop != 0) atomicAdd(&s_drop, my_drop);
+  __syncthreads();
+  const size_t row = (size_t)blockIdx.x * nkeys;
+  for (uint32_t c = tid; c < nkeys; c += kPartThreads) hist[row + c] = s_h[c];
+  if (tid == 0 && dropped != nullptr && s_drop != 0)
+    atomicAdd(dropped, s_drop);
+}
+
+// Running sums of key c over the blocks, in place; returns its total.
+__device__ __forceinline__ uint32_t direct_column(uint32_t* hist, uint32_t nb,
+                                                  uint32_t nkeys, uint32_t c) {
+  uint32_t run = 0, b = 0;
+  for (; b + 16 <= nb; b += 16) {
+    uint32_t v[16];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) v[u] = hist[(size_t)(b + u) * nkeys + c];
+#pragma unroll
+    for (int u = 0; u < 16; ++u) {
+      hist[(size_t)(b + u) * nkeys + c] = run;
+      run += v[u];
+    }
+  }
+  for (; b < nb; ++b) {
+    const uint32_t v = hist[(size_t)b * nkeys + c];
+    hist[(size_t)b * nkeys + c] = run;
+    run += v;
+  }
+  return run;
+}
+
+__global__ __launch_bounds__(64) void k_direct_cols(
+    uint32_t* __restrict__ hist, uint32_t nb, uint32_t nkeys,
+    uint32_t* __restrict__ totals) {
+  const uint32_t c = blockIdx.x * 64u + threadIdx.x;
+  if (c < nkeys) totals[c] = direct_column(hist, nb, nkeys, c);
+}
+
+// One workgroup.  offsets[] holds the key totals (direct_cols), or nothing
+// yet (COLS: the running sums are formed here).
+template <bool COLS>
+__global__ __launch_bounds__(kPartThreads) void k_direct_tiles(
+    Geo g, uint32_t* hist, uint32_t nb, uint32_t nkeys, uint32_t* offsets,
+    TileWork w, BinClear clear) {
+  extern __shared__ uint32_t s_off[];  // nkeys + 1
+  __shared__ uint32_t s_tmp[kPartThreads / 64];
+  __shared__ uint32_t s_ctr[8];
+  __shared__ unsigned long long s_reads;
+  for (uint32_t i = threadIdx.x; i < clear.nstrips; i += kPartThreads)
+    clear.strips[i] = 0u;
+  if (threadIdx.x < 8) s_ctr[threadIdx.x] = 0u;
+  if (threadIdx.x == 0) s_reads = 0ull;
+  for (uint32_t c = threadIdx.x; c < nkeys; c += kPartThreads)
+    s_off[c] = COLS ? direct_column(hist, nb, nkeys, c) : offsets[c];
+  __syncthreads();  // also orders the strip zeros before their marks
+  const uint32_t total = lds_exclusive_scan(s_off, nkeys, s_tmp);
+  if (threadIdx.x == 0) s_off[nkeys] = total;
+  __syncthreads();
+  for (uint32_t c = threadIdx.x; c <= nkeys; c += kPartThreads)
+    offsets[c] = s_off[c];
+  for (int t0 = 0; t0 < g.ntiles; t0 += kPartThreads) {
+    const int t = t0 + (int)threadIdx.x;
+    const bool live = t < g.ntiles;
+    TileRecords r;
+    r.work = 0;
+    if (live) r = tile_records(g, t, w.degrid, s_off);
+    const uint32_t ib = wave_append(&s_ctr[4], live && r.work > 0);
+    const uint32_t ii = wave_append(&s_ctr[5], live && r.work == 0);
+    if (r.work > 0) atomicAdd(&s_reads, (unsigned long long)r.work);
+    if (live) emit_tile(g, w, t, r, r.work > 0 ? ib : ii, s_ctr);
+  }
+  __syncthreads();
+  if (threadIdx.x < 6) w.counters[threadIdx.x] = s_ctr[threadIdx.x];
+  if (threadIdx.x == 6) w.counters[6] = (uint32_t)s_reads;
+  if (threadIdx.x == 7) w.counters[7] = (uint32_t)(s_reads >> 32);
+}
+
+template <typename R, int V>
+__global__ __launch_bounds__(256) void k_direct_scatter(
+    Geo g, VisSource src, int64_t m, const uint2* __restrict__ keyrank,
+    const uint32_t* __restrict__ hist, uint32_t nkeys,
+    const uint32_t* __restrict__ offsets, Record<R>* __restrict__ rec,
+    int degrid, cplx<R>* __restrict__ vis_out) {
+  const int64_t gi = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (gi >= m) return;
+  const uint2 kr = keyrank[gi];
+  if (kr.x == kNoKey) {
+    if (degrid) vis_out[gi] = cplx<R>{(R)0, (R)0};
+    return;
+  }
+  const uint32_t pos =
+      offsets[kr.x] + hist[(size_t)(gi / V) * nkeys + kr.x] + kr.y;
+  rec[pos] = make_record<R>(g, src, gi, degrid);
+}
+
 }  // namespace
 
 // Two-level partition of m visibilities (see the kernels above), in the
@@ -869,6 +1174,13 @@ template <typename R>
 void launch_part_scan1(int64_t m, const PartWork& w, hipStream_t st) {
   constexpr int V = part_block<R>();
   const uint32_t C = w.nbuckets;
+  if (m > 0 && (uint64_t)part_nb1(m, V) * C <= kSmallScan) {
+    hipLaunchKernelGGL(k_part_scan1_small, dim3(1), dim3(kPartThreads),
+                       (size_t)(C + kPartThreads) * 4, st, w.hist1,
+                       part_nb1(m, V), C, (uint32_t)V, w.bounds, w.chunk0,
+                       w.clear);
+    return;
+  }
   const dim3 cg((C + 255) / 256);
   if (m > 0) {
     const uint32_t nb1 = part_nb1(m, V);
@@ -882,7 +1194,7 @@ void launch_part_scan1(int64_t m, const PartWork& w, hipStream_t st) {
     launch_zero_u32(w.bounds, (int64_t)C + 1, st);
   }
   hipLaunchKernelGGL(k_part_bounds, dim3(1), dim3(kPartThreads), 0, st,
-                     w.bounds, C, (uint32_t)V, w.chunk0);
+                     w.bounds, C, (uint32_t)V, w.chunk0, w.clear);
   if (m > 0) {
     const uint32_t nb1 = part_nb1(m, V);
     const uint32_t nseg = nb1 < (uint32_t)kPartSegs ? nb1 : (uint32_t)kPartSegs;
@@ -952,6 +1264,76 @@ WS_INST(float)
 WS_INST(double)
 #undef WS_INST
 
+namespace {
+// Visibilities of one counting workgroup: few enough workgroups that the
+// histograms stay smaller than the records, enough of them for small calls.
+constexpr int kDirectSmall = 1024, kDirectLarge = 4096;
+bool direct_large(int64_t max_vis, int64_t nkeys) {
+  return max_vis > 65536 || nkeys > 4096;
+}
+}  // namespace
+
+int64_t direct_hist_words(int64_t max_vis, int64_t nkeys) {
+  const int V = direct_large(max_vis, nkeys) ? kDirectLarge : kDirectSmall;
+  return (max_vis + V - 1) / V * nkeys;
+}
+
+bool direct_fits(int64_t max_vis, int64_t nkeys) {
+  return nkeys <= kDirectKeys && max_vis <= kDirectVis;
+}
+
+template <typename R>
+void launch_direct_sort(const Geo& g, const VisSource& src, int64_t m,
+                        int64_t max_vis, const DirectWork& w,
+                        const TileWork& tw, const BinClear& clear,
+                        unsigned long long* dropped, void* vis_out,
+                        hipStream_t st) {
+  const bool large = direct_large(max_vis, w.nkeys);
+  const int V = large ? kDirectLarge : kDirectSmall;
+  const uint32_t nb = (uint32_t)((m + V - 1) / V);
+  if (m > 0) {
+    if (large)
+      hipLaunchKernelGGL(k_direct_count<kDirectLarge>, dim3(nb),
+                         dim3(kPartThreads), (size_t)w.nkeys * 4, st, g, src,
+                         m, w.nkeys, w.keyrank, w.hist, dropped);
+    else
+      hipLaunchKernelGGL(k_direct_count<kDirectSmall>, dim3(nb),
+                         dim3(kPartThreads), (size_t)w.nkeys * 4, st, g, src,
+                         m, w.nkeys, w.keyrank, w.hist, dropped);
+  }
+  const size_t lds = (size_t)(w.nkeys + 1) * 4;
+  if ((uint64_t)nb * w.nkeys <= kDirectCols) {
+    hipLaunchKernelGGL(k_direct_tiles<true>, dim3(1), dim3(kPartThreads), lds,
+                       st, g, w.hist, nb, w.nkeys, w.offsets, tw, clear);
+  } else {
+    hipLaunchKernelGGL(k_direct_cols, dim3((w.nkeys + 63) / 64), dim3(64), 0,
+                       st, w.hist, nb, w.nkeys, w.offsets);
+    hipLaunchKernelGGL(k_direct_tiles<false>, dim3(1), dim3(kPartThreads),
+                       lds, st, g, w.hist, nb, w.nkeys, w.offsets, tw, clear);
+  }
+  if (m == 0) return;
+  const dim3 sg((unsigned)((m + 255) / 256));
+  if (large)
+    hipLaunchKernelGGL((k_direct_scatter<R, kDirectLarge>), sg, dim3(256), 0,
+                       st, g, src, m, w.keyrank, w.hist, w.nkeys, w.offsets,
+                       (Record<R>*)w.rec, tw.degrid, (cplx<R>*)vis_out);
+  else
+    hipLaunchKernelGGL((k_direct_scatter<R, kDirectSmall>), sg, dim3(256), 0,
+                       st, g, src, m, w.keyrank, w.hist, w.nkeys, w.offsets,
+                       (Record<R>*)w.rec, tw.degrid, (cplx<R>*)vis_out);
+}
+
+template void launch_direct_sort<float>(const Geo&, const VisSource&, int64_t,
+                                        int64_t, const DirectWork&,
+                                        const TileWork&, const BinClear&,
+                                        unsigned long long*, void*,
+                                        hipStream_t);
+template void launch_direct_sort<double>(const Geo&, const VisSource&,
+                                         int64_t, int64_t, const DirectWork&,
+                                         const TileWork&, const BinClear&,
+                                         unsigned long long*, void*,
+                                         hipStream_t);
+
 int64_t partition_blocks(int64_t max_vis, int elem) {
   const int V = part_block_of(elem);
   return (max_vis + V - 1) / V;
@@ -1016,17 +1398,10 @@ template void launch_bin_scatter<double>(const Geo&, const VisSource&,
                                          const uint32_t*, uint32_t, void*,
                                          int, void*, hipStream_t);
 
-void launch_tile_work(const Geo& g, const uint32_t* offsets, int mode_degrid,
-                      uint32_t chunk, uint32_t* tile_chunks,
-                      uint32_t* tile_slot, uint32_t* counters,
-                      uint32_t* split_list, uint32_t max_slots, uint2* extra,
-                      uint32_t max_extra, uint32_t* busy, uint32_t* idle,
-                      uint32_t* strips, uint32_t* tslot, hipStream_t st) {
+void launch_tile_work(const Geo& g, const uint32_t* offsets,
+                      const TileWork& w, hipStream_t st) {
   const int nb = (g.ntiles + 255) / 256;
-  hipLaunchKernelGGL(k_tile_work, dim3(nb), dim3(256), 0, st, g, offsets,
-                     mode_degrid, chunk, tile_chunks, tile_slot, counters,
-                     split_list, max_slots, extra, max_extra, busy, idle,
-                     strips, tslot);
+  hipLaunchKernelGGL(k_tile_work, dim3(nb), dim3(256), 0, st, g, offsets, w);
 }
 
 }  // namespace ws

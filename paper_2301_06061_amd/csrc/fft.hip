@@ -1106,26 +1106,27 @@ __global__ __launch_bounds__(256) void k_fill_zero_u32(uint32_t* p, int64_t n) {
   for (int64_t t = i; t < n; t += stride) p[t] = 0u;
 }
 
-// Grid-correction table: thread i < nu gives 1 / (c psi(f_i)) for the u
-// axis, thread nu + i gives 1 / psi(f_i) for the v axis.
-__global__ __launch_bounds__(256) void k_correction(Geo g, double* corr) {
+// A plan's tables, one thread per entry of an axis (u, then v): the
+// twiddles e^{2 pi i idx / n}; with g.corr, the grid-correction factors 1 /
+// (c psi(f)) along u and 1 / psi(f) along v; and the 256 bytes of zeros.
+// One launch: the allocation-free call fills them anew each time.
+template <typename R>
+__global__ __launch_bounds__(64) void k_tables(Geo g, cplx<R>* tw_u,
+                                               cplx<R>* tw_v, double* corr,
+                                               uint32_t* zeros) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  if (i < 64) zeros[i] = 0u;
   if (i >= g.nu + g.nv) return;
   const bool u = i < g.nu;
   const int n = u ? g.nu : g.nv;
   const int idx = u ? i : i - g.nu;
+  double sn, cs;
+  sincospi(2.0 * (double)idx / (double)n, &sn, &cs);
+  (u ? tw_u : tw_v)[idx] = cplx<R>{(R)cs, (R)sn};
+  if (g.corr == nullptr) return;
   const double f = (double)(idx - n / 2) / (double)n;
   const double psi = kernel_transform(g.kern, g.K, g.inv2s2, g.es_beta, f);
   corr[i] = 1.0 / ((u ? g.cnorm : 1.0) * psi);
-}
-
-template <typename R>
-__global__ __launch_bounds__(256) void k_twiddles(cplx<R>* tw, int n) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  double sn, cs;
-  sincospi(2.0 * (double)i / (double)n, &sn, &cs);
-  tw[i] = cplx<R>{(R)cs, (R)sn};
 }
 
 // Threads per row transform: enough to cover the N/8 first-stage
@@ -1491,16 +1492,11 @@ void launch_zero_u32(uint32_t* p, int64_t n, hipStream_t st) {
                      p, n);
 }
 
-void launch_correction(const Geo& g, double* corr, hipStream_t st) {
-  const int n = g.nu + g.nv;
-  hipLaunchKernelGGL(k_correction, dim3((n + 255) / 256), dim3(256), 0, st,
-                     g, corr);
-}
-
 template <typename R>
-void launch_twiddles(void* tw, int n, hipStream_t st) {
-  hipLaunchKernelGGL(k_twiddles<R>, dim3((n + 255) / 256), dim3(256), 0, st,
-                     (cplx<R>*)tw, n);
+void launch_tables(const Geo& g, void* tw_u, void* tw_v, double* corr,
+                   uint32_t* zeros, hipStream_t st) {
+  hipLaunchKernelGGL(k_tables<R>, dim3((g.nu + g.nv + 63) / 64), dim3(64), 0,
+                     st, g, (cplx<R>*)tw_u, (cplx<R>*)tw_v, corr, zeros);
 }
 
 #define WS_INST(R)                                                            \
@@ -1527,7 +1523,8 @@ void launch_twiddles(void* tw, int n, hipStream_t st) {
   template void launch_screen_bcast<R>(const void*, int, void*, const Geo&,  \
                                        hipStream_t);                         \
   template void launch_fill_zero<R>(void*, int64_t, hipStream_t);           \
-  template void launch_twiddles<R>(void*, int, hipStream_t);
+  template void launch_tables<R>(const Geo&, void*, void*, double*,         \
+                                 uint32_t*, hipStream_t);
 WS_INST(float)
 WS_INST(double)
 #undef WS_INST

@@ -245,56 +245,14 @@ __device__ __forceinline__ void wave_share(uint32_t f0, uint32_t f1, int w,
   e = min(b + q, f1);
 }
 
-// Work item descriptors: everything the gridder needs to start an item,
-// written by k_item_desc after the tile work pass, so that the gridder
-// starts an item with one load instead of a chain of dependent loads (queue
-// entry -> tile -> its key ranges).  Words: tile, chunks of the tile, chunk,
-// f0, f1, off0, cum[1 .. kSegments-1], step[1 .. kSegments-1].  A tile of
-// one chunk (chunk 0, never an extra item) has its index in the busy list
-// in the chunk word instead: its slot in the busy-tile store.
-static_assert(6 + 2 * (kSegments - 1) == kDescWords, "descriptor layout");
-
-__global__ __launch_bounds__(256) void k_item_desc(
-    Geo g, const uint32_t* __restrict__ offsets,
-    const uint32_t* __restrict__ counters, const uint2* __restrict__ extra,
-    const uint32_t* __restrict__ busy,
-    const uint32_t* __restrict__ tile_chunks, uint32_t chunk,
-    uint32_t* __restrict__ desc, uint32_t max_items) {
-  const uint32_t n = blockIdx.x * 256u + threadIdx.x;
-  if (n >= max_items) return;
-  const uint32_t nextra = counters[2];
-  if (n >= nextra + counters[4]) return;
-  const bool is_extra = n < nextra;
-  const uint32_t tile = is_extra ? extra[n].x : busy[n - nextra];
-  const uint32_t ch = is_extra ? extra[n].y : 0u;
-  const uint32_t nch = tile_chunks[tile];
-  uint32_t lo[kSegments], hi[kSegments];
-  tile_segments(g, (int)tile, lo, hi);
-  uint32_t w[kDescWords];
-  uint32_t cum = 0, prev = 0;
-#pragma unroll
-  for (int s = 0; s < kSegments; ++s) {
-    const uint32_t as = offsets[lo[s]], bs = offsets[hi[s]];
-    const uint32_t off = as - cum;
-    if (s == 0) {
-      w[5] = off;
-    } else {
-      w[5 + s] = cum;
-      w[5 + kSegments - 1 + s] = off - prev;
-    }
-    prev = off;
-    cum += bs - as;
-  }
-  const uint32_t f0 = ch * chunk;
-  w[0] = tile;
-  w[1] = nch;
-  w[2] = nch == 1 ? n - nextra : ch;
-  w[3] = f0;
-  w[4] = nch == 1 ? cum : min(cum, f0 + chunk);
-  uint4* d = reinterpret_cast<uint4*>(desc + (size_t)n * kDescWords);
-#pragma unroll
-  for (int q = 0; q < kDescWords / 4; ++q)
-    d[q] = make_uint4(w[4 * q], w[4 * q + 1], w[4 * q + 2], w[4 * q + 3]);
+// Work item descriptors hold everything the gridder needs to start an item
+// (written by the tile work pass), so that it starts one with one load
+// instead of a chain of dependent loads (queue entry -> tile -> its key
+// ranges).  Index of the descriptor of queue number n: the extra chunks of
+// split tiles come first in the queue, after the busy tiles in the table.
+__device__ __forceinline__ uint32_t desc_index(const Geo& g, uint32_t nextra,
+                                               uint32_t n) {
+  return n < nextra ? (uint32_t)g.ntiles + n : n - nextra;
 }
 
 // A descriptor as loaded (uniform values; left in whatever registers the
@@ -568,11 +526,11 @@ __global__ __launch_bounds__(kGridThreads) void k_grid_tiles(GridJob<R> j) {
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ uint32_t s_next[2];
   GridAcc<R>* s_lds = reinterpret_cast<GridAcc<R>*>(smem);
-  const uint32_t total = item_total(j.counters);
+  const uint32_t total = item_total(j.counters), nextra = j.counters[2];
   clear_lds(s_lds, 2u * (uint32_t)(j.g.T * j.pitch));
   item_loop<R, K, KT>(s_lds, &j.counters[3], s_next, &j,
                   [&](uint32_t n, const GridJob<R>*&, uint32_t& li) {
-                    li = n;
+                    li = desc_index(j.g, nextra, n);
                     return n < total;
                   });
 }
@@ -588,11 +546,13 @@ __global__ __launch_bounds__(kGridThreads) void k_grid_batch(
   extern __shared__ __align__(16) unsigned char smem[];
   __shared__ uint32_t s_next[2];
   __shared__ uint32_t s_base[kMaxBatch + 1];
+  __shared__ uint32_t s_extra[kMaxBatch];
   GridAcc<R>* s_lds = reinterpret_cast<GridAcc<R>*>(smem);
   if (threadIdx.x == 0) {
     uint32_t b = 0;
     for (int p = 0; p < njobs; ++p) {
       s_base[p] = b;
+      s_extra[p] = jobs[p].counters[2];
       b += item_total(jobs[p].counters);
     }
     s_base[njobs] = b;
@@ -606,7 +566,8 @@ __global__ __launch_bounds__(kGridThreads) void k_grid_batch(
                     if (live)
                       while (n >= s_base[p + 1]) ++p;
                     jp = jobs + p;
-                    li = live ? n - s_base[p] : 0u;
+                    li = live ? desc_index(jp->g, s_extra[p], n - s_base[p])
+                              : 0u;
                     return live;
                   });
 }
@@ -929,17 +890,6 @@ void launch_grid_batch(const GridJob<R>* jobs, int njobs, int K, int kern,
                        int cus, hipStream_t st) {
   WS_K_SWITCH(K, kern, (grid_batch_k<R, KK, KT>(jobs, njobs, lds, queue,
                                                 max_items, cus, st)));
-}
-
-void launch_item_desc(const Geo& g, const uint32_t* offsets,
-                      const uint32_t* counters, const uint2* extra,
-                      const uint32_t* busy, const uint32_t* tile_chunks,
-                      uint32_t chunk, uint32_t* desc, uint32_t max_items,
-                      hipStream_t st) {
-  if (max_items == 0) return;
-  hipLaunchKernelGGL(k_item_desc, dim3((max_items + 255) / 256), dim3(256),
-                     0, st, g, offsets, counters, extra, busy, tile_chunks,
-                     chunk, desc, max_items);
 }
 
 template <typename R>

@@ -39,6 +39,13 @@ struct VisSource {
 void launch_bin_count(const Geo& g, const VisSource& src, int64_t m,
                       uint32_t* copies, uint32_t nkeys, uint2* keyrank,
                       unsigned long long* dropped, hipStream_t st);
+// Tile work counters (16 words) and strip marks (nstrips words, 0: left as
+// they are) that a binning kernel clears before the tile work pass.
+struct BinClear {
+  uint32_t* counters;
+  uint32_t* strips;
+  uint32_t nstrips;
+};
 // Two-level partition (bin.hip): the same records and key offsets as the
 // counting sort above, with no global atomics.  Buckets hold `span` keys
 // each (a plane and a group of tile rows; nbuckets * span = all keys).
@@ -60,6 +67,7 @@ struct PartWork {
   uint32_t* hist2x;    // [chunks][span] each chunk's exclusive scan
   uint32_t* offsets;   // [nkeys + 1] record offset of every key
   void* rec;           // [max_vis] final records in key order
+  BinClear clear;
 };
 // Phases, in order: level-1 counts; the bucket-major scan and the
 // level-2 chunks; the level-1 scatter; level-2 counts; level-2 scan (writes
@@ -97,13 +105,46 @@ void launch_bin_scatter(const Geo& g, const VisSource& src, int64_t m,
                         const uint2* keyrank, const uint32_t* offsets,
                         uint32_t nkeys, void* records, int degrid,
                         void* vis_out, hipStream_t st);
-// tslot (optional): busy-list index of every tile with records.
-void launch_tile_work(const Geo& g, const uint32_t* offsets, int mode_degrid,
-                      uint32_t chunk, uint32_t* tile_chunks,
-                      uint32_t* tile_slot, uint32_t* counters,
-                      uint32_t* split_list, uint32_t max_slots, uint2* extra,
-                      uint32_t max_extra, uint32_t* busy, uint32_t* idle,
-                      uint32_t* strips, uint32_t* tslot, hipStream_t st);
+// Everything the tile work pass writes: per tile its chunk count and first
+// scratch slot; the busy, idle, split and extra-chunk lists with their
+// counters; strip marks (or null); busy-list index of every tile with
+// records (tslot, or null); gridding: one descriptor per work item, the
+// first chunk of busy tile i at i, extra item e at ntiles + e.
+struct TileWork {
+  int degrid;
+  uint32_t chunk;  // records per work item
+  uint32_t max_slots, max_extra;
+  uint32_t* tile_chunks;
+  uint32_t* tile_slot;
+  uint32_t* counters;
+  uint32_t* split_list;
+  uint2* extra;
+  uint32_t* busy;
+  uint32_t* idle;
+  uint32_t* strips;
+  uint32_t* tslot;
+  uint32_t* desc;
+};
+void launch_tile_work(const Geo& g, const uint32_t* offsets,
+                      const TileWork& w, hipStream_t st);
+
+// Direct sort of a small plan (bin.hip): records and key offsets as above,
+// and the tile work pass with it.
+struct DirectWork {
+  uint32_t nkeys;
+  uint2* keyrank;     // [max_vis]
+  uint32_t* hist;     // direct_hist_words(max_vis, nkeys)
+  uint32_t* offsets;  // [nkeys + 1]
+  void* rec;          // [max_vis]
+};
+bool direct_fits(int64_t max_vis, int64_t nkeys);
+int64_t direct_hist_words(int64_t max_vis, int64_t nkeys);
+template <typename R>
+void launch_direct_sort(const Geo& g, const VisSource& src, int64_t m,
+                        int64_t max_vis, const DirectWork& w,
+                        const TileWork& tw, const BinClear& clear,
+                        unsigned long long* dropped, void* vis_out,
+                        hipStream_t st);
 
 // gridding and degridding (grid.hip)
 // LDS accumulator of the gridder: FP64 for both paths.  On gfx950 the
@@ -138,7 +179,7 @@ struct GridJob {
   const uint32_t* tile_chunks;
   const uint32_t* tile_slot;
   const Record<R>* rec;
-  const uint32_t* desc;       // item descriptors (kDescWords words each)
+  const uint32_t* desc;       // item descriptors (TileWork::desc)
   cplx<R>* planes;
   cplx<GridAcc<R>>* partials;  // tiles of split items, unrounded
   int accumulate;
@@ -161,14 +202,13 @@ __host__ __device__ inline size_t tile_store_at(int T, int row, int col) {
   return (size_t)(col / B) * T * B + (size_t)row * B + (col % B);
 }
 
-// Descriptors of the gridding work items (after launch_tile_work), one
-// per item in queue order; desc holds max_items * kDescWords words.
+// Words of a gridding work item's descriptor: tile, chunks of the tile,
+// chunk, f0, f1, off0, cum[1 .. kSegments-1], step[1 .. kSegments-1] (see
+// GridItem).  A tile of one chunk (chunk 0, never an extra item) has its
+// index in the busy list in the chunk word instead: its slot in the
+// busy-tile store.
 constexpr int kDescWords = 24;
-void launch_item_desc(const Geo& g, const uint32_t* offsets,
-                      const uint32_t* counters, const uint2* extra,
-                      const uint32_t* busy, const uint32_t* tile_chunks,
-                      uint32_t chunk, uint32_t* desc, uint32_t max_items,
-                      hipStream_t st);
+static_assert(6 + 2 * (kSegments - 1) == kDescWords, "descriptor layout");
 template <typename R>
 void launch_grid_tiles(const GridJob<R>& j, uint32_t max_items, int cus,
                        hipStream_t st);
@@ -252,8 +292,6 @@ void launch_wcorrect(const void* F, void* img, const Geo& g, hipStream_t st);
 template <typename R>
 void launch_fill_zero(void* p, int64_t n, hipStream_t st);
 void launch_zero_u32(uint32_t* p, int64_t n, hipStream_t st);
-template <typename R>
-void launch_twiddles(void* tw, int n, hipStream_t st);
 // Imaging major cycle (clean.hip).  Device state of one Hogbom minor
 // cycle and the per-block argmax slots it reduces.
 struct CleanState {
@@ -284,9 +322,12 @@ void launch_clean_minor(void* d, const void* beam, void* model, int nu,
                         CleanState* state, CleanSlot* slots, int nslots,
                         int32_t* picks, int32_t* n_done, hipStream_t st);
 
-// Grid-correction table of a plan (g.corr must point at nu + nv doubles):
-// corr[p] = 1 / (c psi(f_p)), corr[nu + q] = 1 / psi(f_q), f = (index -
-// n/2) / n, psi the kernel's 1-D transform (kernel_transform).
-void launch_correction(const Geo& g, double* corr, hipStream_t st);
+// A plan's tables: twiddles of both axes; where g.corr is set (to corr),
+// the grid-correction factors corr[p] = 1 / (c psi(f_p)), corr[nu + q] = 1 /
+// psi(f_q), f = (index - n/2) / n, psi the kernel's 1-D transform
+// (kernel_transform); 64 zero words.
+template <typename R>
+void launch_tables(const Geo& g, void* tw_u, void* tw_v, double* corr,
+                   uint32_t* zeros, hipStream_t st);
 
 }  // namespace ws
