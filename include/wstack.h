@@ -214,8 +214,8 @@ ws_status ws_image_accumulate(ws_plan* plan, void* image);
  * scratch: the same image as ws_grid_visibilities() followed by
  * ws_image_accumulate(), to rounding.  Because no caller observes the
  * stack in between, tiles that receive no visibility are not zeroed when
- * the imaging pass can take them as zero by itself (tile edge 64, nu in
- * [512, 4096], nv <= 4096); otherwise the call does exactly the two steps.
+ * the imaging pass can take them as zero by itself (tile edge 64; not for
+ * 32768-point FP64 rows); otherwise the call does exactly the two steps.
  * Arguments as for those two calls; the plan must be empty (after init or
  * ws_plan_reset(), else WS_BAD_STATE) and is empty afterwards, with the
  * stack's contents unspecified. */

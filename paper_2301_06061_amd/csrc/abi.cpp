@@ -42,8 +42,8 @@ constexpr int kMaxN = 32768;
 // Largest column length transformed in one pass (whole column blocks in
 // LDS); longer columns use the four-step transform.
 constexpr int kOnePassCols = 4096;
-// Largest row length of the fused row-transform + screen kernels.
-constexpr int kFusedRows = 4096;
+// Longest rows of plans with a busy-tile store.
+constexpr int kStoreRows = 4096;
 constexpr int kMinN = 16;
 constexpr int kMaxSupport = 15;
 constexpr int64_t kMaxVis = (int64_t(1) << 31) - 1;
@@ -314,7 +314,7 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
   // records beyond that stay in the stack; each visibility is read by at
   // most four tiles), and the slot of every tile.
   L->tstore = L->elem == 8 && p->nv == 4096 && L->T == 64 && p->nu >= 512 &&
-              p->nu <= kFusedRows;
+              p->nu <= kStoreRows;
   L->tstore_slots =
       L->tstore ? std::max<int64_t>(
                       1, std::min<int64_t>(L->ntiles / 2, 4 * max_vis))
@@ -740,7 +740,7 @@ ws_status image_impl(ws_plan* pl, void* image, bool lazy = false,
                       lazy || marked ? pl->w<uint32_t>(pl->L.o_chunks)
                                      : nullptr,
                       lazy && ts));
-  if (p.nu <= kFusedRows) {
+  if (rows_can_fuse(p.nu, pl->L.elem)) {
     bool ok = true;
     WS_TRY(launch(pl, "row_screen_sum", [&] {
       ok = launch_row_screen_sum<R>(pl->planes, image, g,
@@ -766,7 +766,7 @@ ws_status degrid_impl(ws_plan* pl, const void* image, int image_is_real,
   const ws_params& p = pl->p;
   const Layout& L = pl->L;
   Geo g = pl->g;
-  if (p.nu <= kFusedRows) {
+  if (rows_can_bcast(p.nu, pl->L.elem)) {
     bool ok = true;
     WS_TRY(launch(pl, "screen_row_bcast", [&] {
       ok = launch_screen_row_bcast<R>(image, image_is_real, pl->planes,
@@ -803,27 +803,26 @@ bool aligned(const void* p, size_t a) {
 }
 
 // Tiles without records may stay unwritten only where every later read
-// knows them: one-pass columns with tile-wide blocks and the fused rows
-// reading by strip marks (tile edge 64, rows of 512 or more).
+// knows them: one-pass columns reading by tile counts and the fused rows
+// reading by strip marks (tile edge 64).
 bool lazy_ok(const ws_plan* pl) {
-  return pl->g.T == 64 && pl->p.nv <= kOnePassCols && pl->p.nu >= 512 &&
-         pl->p.nu <= kFusedRows;
+  return pl->g.T == 64 && pl->p.nv <= kOnePassCols &&
+         rows_can_fuse(pl->p.nu, pl->L.elem);
 }
 
 // A first gridding call that only the fused imaging reads may put its
 // tiles with records in the busy-tile store (where the layout has one).
 bool tstore_ok(const ws_plan* pl) { return lazy_ok(pl) && pl->L.tstore; }
 
-// Beyond 4096 the one-call path leaves the tiles without records
-// unwritten too: the column transform (one-pass or the first four-step
-// step) reads by tile record counts and skips unmarked strips, and the
-// row transform (fused below 4096 columns, else by strip marks) takes the
-// unmarked strips as zero.
+// Beyond that the one-call path leaves the tiles without records unwritten
+// too: the column transform (one-pass or the first four-step step) reads by
+// tile record counts and skips unmarked strips, and the row transform (fused,
+// else by strip marks) takes the unmarked strips as zero.
 bool marked_ok(const ws_plan* pl) {
   const ws_params& p = pl->p;
-  return !lazy_ok(pl) && pl->g.T == 64 && p.nu >= 1024 &&
-         (p.nu > kFusedRows || p.nv > kOnePassCols) &&
-         (p.nu <= kFusedRows || fft_rows_can_mask(p.nu, pl->L.elem));
+  return !lazy_ok(pl) && pl->g.T == 64 &&
+         (rows_can_fuse(p.nu, pl->L.elem) ||
+          fft_rows_can_mask(p.nu, pl->L.elem));
 }
 
 ws_status check_plan(ws_plan* pl) {

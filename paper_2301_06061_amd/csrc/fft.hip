@@ -76,9 +76,48 @@ __device__ __forceinline__ void dft8(cplx<R>* v, R s) {
   v[7] = csub(e[3], o3);
 }
 
+template <typename R>
+__device__ __forceinline__ void dft16(cplx<R>* v, R s) {
+  // n = 4 n1 + n2, k = k1 + 4 k2: length-4 transforms over n1, the twiddles
+  // W16^(n2 k1), length-4 transforms over n2.
+  const R h = (R)0.70710678118654752440084436210484903928;
+  const R c = (R)0.92387953251128675612818318939678828682;  // cos(pi / 8)
+  const R d = (R)0.38268343236508977172845998403039886676;  // sin(pi / 8)
+  cplx<R> y[4][4];
+#pragma unroll
+  for (int n2 = 0; n2 < 4; ++n2) {
+    cplx<R> t[4] = {v[n2], v[4 + n2], v[8 + n2], v[12 + n2]};
+    dft4(t, s);
+#pragma unroll
+    for (int k1 = 0; k1 < 4; ++k1) y[k1][n2] = t[k1];
+  }
+  auto w2 = [&](cplx<R> a) -> cplx<R> {  // times e^{s 2 pi i 2/16}
+    return {h * (a.re - s * a.im), h * (a.im + s * a.re)};
+  };
+  auto w6 = [&](cplx<R> a) -> cplx<R> {  // times e^{s 2 pi i 6/16}
+    return {h * (-a.re - s * a.im), h * (s * a.re - a.im)};
+  };
+  y[1][1] = cmul(y[1][1], cplx<R>{c, s * d});
+  y[1][2] = w2(y[1][2]);
+  y[1][3] = cmul(y[1][3], cplx<R>{d, s * c});
+  y[2][1] = w2(y[2][1]);
+  y[2][2] = rot_i(y[2][2], s);
+  y[2][3] = w6(y[2][3]);
+  y[3][1] = cmul(y[3][1], cplx<R>{d, s * c});
+  y[3][2] = w6(y[3][2]);
+  y[3][3] = cmul(y[3][3], cplx<R>{-c, -s * d});
+#pragma unroll
+  for (int k1 = 0; k1 < 4; ++k1) {
+    dft4(y[k1], s);
+#pragma unroll
+    for (int k2 = 0; k2 < 4; ++k2) v[k1 + 4 * k2] = y[k1][k2];
+  }
+}
+
 template <typename R, int RAD>
 __device__ __forceinline__ void dft(cplx<R>* v, R s) {
-  if constexpr (RAD == 8) dft8(v, s);
+  if constexpr (RAD == 16) dft16(v, s);
+  else if constexpr (RAD == 8) dft8(v, s);
   else if constexpr (RAD == 4) dft4(v, s);
   else dft2(v);
 }
@@ -87,13 +126,26 @@ __device__ __forceinline__ void dft(cplx<R>* v, R s) {
 // for lo < 64 and e^{2 pi i 64 hi/N}, both rounded from FP64 values.
 template <typename R>
 struct Twiddles {
-  static constexpr bool kTable = false;
   const cplx<R>* t_lo;
   const cplx<R>* t_hi;
   __device__ __forceinline__ cplx<R> operator()(int idx, R s) const {
     const cplx<R> a = t_lo[idx & 63], b = t_hi[idx >> 6];
     const cplx<R> w = cmul(a, b);
     return {w.re, s * w.im};
+  }
+  // w[i] = W^(i k N / (NS RAD)), i = 1, 2, 4, 8 < RAD, of stage P: lookups
+  // of i = 1 and, for radix 16, i = 4; the others as squares (a few units in
+  // the last place).
+  template <int LOGN, bool WIDE, int P, int RAD, int NS>
+  __device__ __forceinline__ void stage(int k, R s, cplx<R>* w) const {
+    constexpr int step = (1 << LOGN) / (NS * RAD);
+    w[1] = (*this)(k * step, s);
+    if constexpr (RAD > 2) w[2] = cmul(w[1], w[1]);
+    if constexpr (RAD == 8) w[4] = cmul(w[2], w[2]);
+    if constexpr (RAD == 16) {
+      w[4] = (*this)(4 * k * step, s);
+      w[8] = cmul(w[4], w[4]);
+    }
   }
 };
 
@@ -137,77 +189,110 @@ constexpr int lds_line(int bc) {
   return (N + (N + 31) / 32) * bc;
 }
 
-// Pass structure of a length-2^LOGN transform: radix 8, the remainder
-// (radix 2 or 4) last; NS = product of the earlier radices.
-constexpr int stage_npass(int logn) { return logn / 3 + (logn % 3 ? 1 : 0); }
-constexpr int stage_rad(int logn, int P) {
-  return P < logn / 3 ? 8 : (logn % 3 == 1 ? 2 : 4);
+// Pass structure of a length-2^LOGN transform, as bits per stage: radix 8 and
+// the remainder (radix 2 or 4) last; or, WIDE (LOGN >= 10), radix 16 first
+// and radix 8 after, as few stages as possible.  Every stage but the first
+// costs a write and a read of the line in LDS, which is what bounds these
+// kernels (measured per CU and wavefront instruction: 8-byte LDS write 7.1
+// cycles, read 4.4, FP32 fma 0.7): 16 x 16 x 16 exchanges a 4096-point line
+// twice, 8 x 8 x 8 x 8 three times.  WIDE needs 16 elements a thread.
+constexpr bool plan_wide(int logn, bool wide) { return wide && logn >= 10; }
+constexpr int stage_bits(int logn, bool wide, int P) {
+  if (plan_wide(logn, wide)) return P < (logn - 10) % 3 + 1 ? 4 : 3;
+  return P < logn / 3 ? 3 : logn % 3;
 }
-constexpr int stage_ns(int logn, int P) { return 1 << (3 * P); }
+constexpr int stage_log_ns(int logn, bool wide, int P) {
+  int b = 0;
+  for (int q = 0; q < P; ++q) b += stage_bits(logn, wide, q);
+  return b;
+}
+constexpr int stage_npass(int logn, bool wide) {
+  int P = 0;
+  while (stage_log_ns(logn, wide, P) < logn) ++P;
+  return P;
+}
 // Offset of stage P's entries in a stage twiddle table (stages 1 ..).
-constexpr int stage_tw_off(int logn, int P) {
+constexpr int stage_tw_off(int logn, bool wide, int P) {
   int o = 0;
   for (int q = 1; q < P; ++q)
-    o += (stage_rad(logn, q) - 1) * stage_ns(logn, q);
+    o += stage_bits(logn, wide, q) << stage_log_ns(logn, wide, q);
   return o;
 }
-constexpr int stage_tw_total(int logn) {
-  return stage_tw_off(logn, stage_npass(logn));
+constexpr int stage_tw_total(int logn, bool wide) {
+  return stage_tw_off(logn, wide, stage_npass(logn, wide));
 }
 
-// Twiddles of every stage held whole in LDS: stage P keeps
-// W^(r k N / (NS RAD)) for r = 1 .. RAD-1, k < NS at
-// tab[stage_tw_off(P) + (r - 1) NS + k] (lanes read consecutive k), the
-// transform sign applied when the table is filled.  One LDS read per
-// twiddle instead of a lookup and the powers of W^k: fewer vector
-// instructions for kernels that transform many lines per table fill.
+// Twiddles of every stage in LDS: stage P keeps W^(i k N / (NS RAD)) for i =
+// 1, 2, 4, (8) < RAD and k < NS at tab[stage_tw_off(P) + log2(i) NS + k]
+// (lanes read consecutive k), the transform sign applied when the table is
+// filled; the other powers are one or two products of these.
 template <typename R>
 struct TableTwiddles {
-  static constexpr bool kTable = true;
   const cplx<R>* tab;
+  template <int LOGN, bool WIDE, int P, int RAD, int NS>
+  __device__ __forceinline__ void stage(int k, R, cplx<R>* w) const {
+    constexpr int OFF = stage_tw_off(LOGN, WIDE, P);
+    w[1] = tab[OFF + k];
+    if constexpr (RAD > 2) w[2] = tab[OFF + NS + k];
+    if constexpr (RAD > 4) w[4] = tab[OFF + 2 * NS + k];
+    if constexpr (RAD > 8) w[8] = tab[OFF + 3 * NS + k];
+  }
 };
 
-// Fills the stage table of a length-2^LOGN transform from the line's
-// global table tw (W_N^i, i < N), conjugated for s = -1.  With
-// `centred_in`, the last stage's entries also carry (-1)^r: a (-1)^e input
+// Fills the stage table of a length-2^LOGN transform from the global table
+// tw of a length-(stride 2^LOGN) one, conjugated for s = -1.  With
+// `centred_in`, the last stage's entries also carry (-1)^i: a (-1)^e input
 // centring gives every butterfly of the earlier stages one common sign,
-// which the radix-8 Stockham order carries to input r of the last stage
-// as (-1)^r, so the input needs no sign flips of its own.
-template <typename R, int LOGN>
+// which the Stockham order carries to input r of the last stage as (-1)^r,
+// so the input needs no sign flips of its own.
+template <typename R, int LOGN, bool WIDE>
 __device__ __forceinline__ void fill_stage_twiddles(cplx<R>* tab,
                                                     const cplx<R>* tw, R s,
-                                                    bool centred_in) {
+                                                    bool centred_in,
+                                                    int stride = 1) {
   constexpr int N = 1 << LOGN;
-  constexpr int NPASS = stage_npass(LOGN);
-  for (int i = threadIdx.x; i < stage_tw_total(LOGN); i += blockDim.x) {
+  constexpr int NPASS = stage_npass(LOGN, WIDE);
+  for (int i = threadIdx.x; i < stage_tw_total(LOGN, WIDE); i += blockDim.x) {
     int idx = 0;
     bool neg = false;
 #pragma unroll
     for (int P = 1; P < NPASS; ++P) {
-      const int off = stage_tw_off(LOGN, P), ns = stage_ns(LOGN, P);
-      const int rad = stage_rad(LOGN, P);
-      if (i >= off && i < off + (rad - 1) * ns) {
-        const int r = (i - off) / ns + 1, k = (i - off) % ns;
-        idx = (r * k * (N / (ns * rad))) & (N - 1);
-        neg = centred_in && P == NPASS - 1 && (r & 1);
+      const int off = stage_tw_off(LOGN, WIDE, P);
+      const int lns = stage_log_ns(LOGN, WIDE, P);
+      const int bits = stage_bits(LOGN, WIDE, P);
+      if (i >= off && i < off + (bits << lns)) {
+        const int l = (i - off) >> lns, k = (i - off) & ((1 << lns) - 1);
+        idx = ((k << l) << (LOGN - lns - bits)) & (N - 1);
+        neg = centred_in && P == NPASS - 1 && l == 0;
       }
     }
-    const cplx<R> w = tw[idx];
+    const cplx<R> w = tw[(size_t)idx * stride];
     tab[i] = neg ? cplx<R>{-w.re, -s * w.im} : cplx<R>{w.re, s * w.im};
   }
+}
+
+// Inputs r = 1 .. RAD-1 of a butterfly times w[1]^r, from w[1], w[2], w[4],
+// w[8].
+template <typename R, int RAD>
+__device__ __forceinline__ void apply_twiddles(cplx<R>* v, cplx<R>* w) {
+#pragma unroll
+  for (int i = 1; i < RAD; i *= 2) {
+#pragma unroll
+    for (int r = i + 1; r < 2 * i; ++r) w[r] = cmul(w[r - i], w[i]);
+  }
+#pragma unroll
+  for (int r = 1; r < RAD; ++r) v[r] = cmul(v[r], w[r]);
 }
 
 // Stage P of a length-2^LOGN Stockham FFT over BC interleaved columns
 // (element e of column c at lds[e * BC + c]).  Stage 0 reads through
 // ld(e, c); the last stage hands each output to st(e, c, it, r, value).
-template <typename R, int LOGN, int BC, int NT, int P>
+template <typename R, int LOGN, int BC, int NT, int P, bool WIDE = false>
 struct Stage {
   static constexpr int N = 1 << LOGN;
-  static constexpr int NP8 = LOGN / 3;
-  static constexpr int REM = LOGN % 3;
-  static constexpr int NPASS = NP8 + (REM ? 1 : 0);
-  static constexpr int RAD = P < NP8 ? 8 : (REM == 1 ? 2 : 4);
-  static constexpr int NS = 1 << (3 * P);
+  static constexpr int NPASS = stage_npass(LOGN, WIDE);
+  static constexpr int RAD = 1 << stage_bits(LOGN, WIDE, P);
+  static constexpr int NS = 1 << stage_log_ns(LOGN, WIDE, P);
   static constexpr int NB = N / RAD;
   static constexpr int TPC = NT / BC;
   static constexpr int IT = (NB + TPC - 1) / TPC;
@@ -217,9 +302,9 @@ struct Stage {
   template <class Load, class Store, class TW>
   __device__ __forceinline__ static void run(cplx<R>* lds, const Load& ld,
                                              const Store& st, const TW& tw,
-                                             R s) {
-    const int c = threadIdx.x % BC;
-    const int jt = threadIdx.x / BC;
+                                             R s, int tid) {
+    const int c = tid % BC;
+    const int jt = tid / BC;
     cplx<R> v[IT][RAD];
 #pragma unroll
     for (int it = 0; it < IT; ++it) {
@@ -239,29 +324,11 @@ struct Stage {
       const int j = jt + it * TPC;
       if (NB % TPC == 0 || j < NB) {
         const int k = j & (NS - 1);
-        if constexpr (NS > 1 && TW::kTable) {
-          constexpr int OFF = stage_tw_off(LOGN, P);
-#pragma unroll
-          for (int r = 1; r < RAD; ++r)
-            v[it][r] = cmul(v[it][r], tw.tab[OFF + (r - 1) * NS + k]);
-        } else if constexpr (NS > 1) {
-          // Twiddles W^(r k N / (NS RAD)), r = 1 .. RAD-1, as powers of the
-          // r = 1 value (one table lookup per butterfly; at most three
-          // products deep, a few units in the last place).
+        if constexpr (NS > 1) {
+          // Twiddles W^(r k N / (NS RAD)), r = 1 .. RAD-1.
           cplx<R> w[RAD];
-          w[1] = tw(k * (N / (NS * RAD)), s);
-          if constexpr (RAD > 2) {
-            w[2] = cmul(w[1], w[1]);
-            w[3] = cmul(w[2], w[1]);
-          }
-          if constexpr (RAD > 4) {
-            w[4] = cmul(w[2], w[2]);
-            w[5] = cmul(w[4], w[1]);
-            w[6] = cmul(w[4], w[2]);
-            w[7] = cmul(w[4], w[3]);
-          }
-#pragma unroll
-          for (int r = 1; r < RAD; ++r) v[it][r] = cmul(v[it][r], w[r]);
+          tw.template stage<LOGN, WIDE, P, RAD, NS>(k, s, w);
+          apply_twiddles<R, RAD>(v[it], w);
         }
         dft<R, RAD>(v[it], s);
         if constexpr (LAST) {
@@ -277,16 +344,26 @@ struct Stage {
     }
     if constexpr (!LAST) {
       __syncthreads();
-      Stage<R, LOGN, BC, NT, P + 1>::run(lds, ld, st, tw, s);
+      Stage<R, LOGN, BC, NT, P + 1, WIDE>::run(lds, ld, st, tw, s, tid);
     }
   }
 };
 
-template <typename R, int LOGN, int BC, int NT, class Load, class Store,
-          class TW>
+// NT threads (tid = 0 .. NT-1 within the line's group; every group of the
+// workgroup calls together) transform one line, or BC interleaved columns.
+template <typename R, int LOGN, int BC, int NT, bool WIDE = false, class Load,
+          class Store, class TW>
+__device__ __forceinline__ void fft_line(cplx<R>* lds, const Load& ld,
+                                         const Store& st, const TW& tw, R s,
+                                         int tid) {
+  Stage<R, LOGN, BC, NT, 0, WIDE>::run(lds, ld, st, tw, s, tid);
+}
+
+template <typename R, int LOGN, int BC, int NT, bool WIDE = false, class Load,
+          class Store, class TW>
 __device__ __forceinline__ void fft_line(cplx<R>* lds, const Load& ld,
                                          const Store& st, const TW& tw, R s) {
-  Stage<R, LOGN, BC, NT, 0>::run(lds, ld, st, tw, s);
+  Stage<R, LOGN, BC, NT, 0, WIDE>::run(lds, ld, st, tw, s, (int)threadIdx.x);
 }
 
 template <typename R>
@@ -869,6 +946,21 @@ struct Screen {
   }
 };
 
+// The phasor of plane 0 and the step between planes of pixel (p, q), as
+// Screen forms them.
+template <typename R>
+__device__ __forceinline__ cplx<R> screen_at(const Geo& g, int p, int q,
+                                             bool odd) {
+  const cplx<double> a =
+      turns_phasor(fma(g.w0, n_minus_one(g, p, q), odd ? 0.5 : 0.0));
+  return {(R)a.re, (R)a.im};
+}
+template <typename R>
+__device__ __forceinline__ cplx<R> screen_step(const Geo& g, int p, int q) {
+  const cplx<double> b = turns_phasor(g.dw * n_minus_one(g, p, q));
+  return {(R)b.re, (R)b.im};
+}
+
 // The plane sum sum_k F_k ph_0 step^k by Horner's rule, planes taken last
 // to first: acc <- acc * step + F_k, and ph_0 * acc once at the end.  The
 // same products as handing out ph_k (the contribution of plane k is
@@ -910,164 +1002,280 @@ __global__ __launch_bounds__(256) void k_wcorrect(const cplx<R>* __restrict__ F,
   img[pix] = cadd(img[pix], corrected(g, p, q, cmul(sc.ph, acc)));
 }
 
-// Row transform of every plane + screen + plane sum into image row q.
-template <typename R, int LOGN, int NT>
-__global__ __launch_bounds__(NT, sizeof(R) == 4 ? 4 : 1) void k_row_screen_sum(
-    const cplx<R>* __restrict__ planes, cplx<R>* __restrict__ img, Geo g,
-    const cplx<R>* __restrict__ tw, const uint32_t* __restrict__ strips) {
-  constexpr int N = 1 << LOGN;
-  using L = Stage<R, LOGN, 1, NT, (LOGN / 3) + ((LOGN % 3) ? 1 : 0) - 1>;
-  constexpr int IT = L::IT, RAD = L::RAD, NB = L::NB;
-  __shared__ cplx<R> lds[lds_line<N>(1)];
-  __shared__ cplx<R> s_tab[stage_tw_total(LOGN)];
-  const int q = blockIdx.x;
-  // Stage twiddles in LDS, the input centring folded into the last stage;
-  // the output centring (-1)^p is half a turn in the screen phase (p has
-  // the parity of the thread index: NT and NB are even).
-  fill_stage_twiddles<R, LOGN>(s_tab, tw, (R)1, true);
-  __syncthreads();
-  const TableTwiddles<R> twl{s_tab};
-  static_assert(NT % 2 == 0 && NB % 2 == 0, "output parity per thread");
-  const bool odd = (threadIdx.x & 1) != 0;
-  cplx<R> acc[IT][RAD];
-  Screen<R> sc[IT][RAD];
-#pragma unroll
-  for (int it = 0; it < IT; ++it)
-#pragma unroll
-    for (int r = 0; r < RAD; ++r) {
-      const int p = threadIdx.x + it * NT + r * NB;
-      acc[it][r] = {(R)0, (R)0};
-      if (NB % NT == 0 || threadIdx.x + it * NT < NB)
-        sc[it][r].init(g, p, q, false, odd);
-    }
-  // Row q of the next plane (k - 1) can be loaded into registers while
-  // plane k is being transformed, so the HBM reads overlap the LDS stages.
-  using F0 = Stage<R, LOGN, 1, NT, 0>;
-  constexpr int IT0 = F0::IT, RAD0 = F0::RAD, NB0 = F0::NB;
-  // FP32: two workgroups per CU (register-capped) overlap each other's
-  // loads, so no register prefetch; FP64 runs one and prefetches.
-  constexpr bool kPrefetch = sizeof(R) == 8;
-  cplx<R> cur[IT0][RAD0], nxt[IT0][RAD0];
-  // Column-strip marks (non-null; used when T is 64, so that the 64
-  // samples one wavefront loads lie in one strip): samples of strips that
-  // hold no data are not read, since gridding left those columns zero and
-  // the column transform kept them so.  The marks of the next plane are
-  // loaded (uniform loads, issued together) while plane k is transformed.
-  const bool skip = g.T == 64 && NB0 % 64 == 0;
-  auto marks = [&](int k, uint32_t (&on)[IT0][RAD0]) {
-    const uint32_t* sp = strips + (size_t)(k < g.nw ? k : 0) * g.tiles_u;
-#pragma unroll
-    for (int it = 0; it < IT0; ++it)
-#pragma unroll
-      for (int r = 0; r < RAD0; ++r) {
-        const uint32_t e = threadIdx.x + it * NT + r * NB0;
-        on[it][r] = skip ? sp[uniform_u32(e >> 6)] : 1u;
-      }
-  };
-  auto fetch = [&](int k, const uint32_t (&on)[IT0][RAD0],
-                   cplx<R> (&buf)[IT0][RAD0]) {
-    const cplx<R>* line = planes + ((size_t)k * g.nv + stack_row(g, q)) * N;
-#pragma unroll
-    for (int it = 0; it < IT0; ++it)
-#pragma unroll
-      for (int r = 0; r < RAD0; ++r) {
-        const int j = threadIdx.x + it * NT;
-        if (NB0 % NT == 0 || j < NB0)
-          buf[it][r] = on[it][r] != 0u ? line[j + r * NB0]
-                                       : cplx<R>{(R)0, (R)0};
-      }
-  };
-  // Planes last to first (Horner's rule for the screen, horner_step).
-  uint32_t on[IT0][RAD0], on_next[IT0][RAD0];
-  marks(g.nw - 1, on);
-  if (kPrefetch) fetch(g.nw - 1, on, cur);
-  for (int k = g.nw - 1; k >= 0; --k) {
-    marks(k > 0 ? k - 1 : 0, on_next);
-    if (kPrefetch && k > 0) fetch(k - 1, on_next, nxt);
-    if (!kPrefetch) fetch(k, on, cur);
-    auto ld = [&](int, int, int it, int r) { return cur[it][r]; };
-    auto st = [&](int, int, int it, int r, cplx<R> v) {
-      acc[it][r] = horner_step(acc[it][r], sc[it][r].step, v);
-    };
-    fft_line<R, LOGN, 1, NT>(lds, ld, st, twl, (R)1);
-    if (kPrefetch) {
-#pragma unroll
-      for (int it = 0; it < IT0; ++it)
-#pragma unroll
-        for (int r = 0; r < RAD0; ++r) cur[it][r] = nxt[it][r];
-    }
-#pragma unroll
-    for (int it = 0; it < IT0; ++it)
-#pragma unroll
-      for (int r = 0; r < RAD0; ++r) on[it][r] = on_next[it][r];
+// Shape of the fused row kernels.
+//   NT     threads a line: 8 points each, and radix-8 stages, so that 16
+//          wavefronts (FP32) share a CU.  4096 x 4096 x 32 planes, ms: FP32
+//          0.96 (16 points each and radix-16 stages: fewer LDS exchanges but
+//          half the wavefronts, 1.01), FP64 1.96.  8192-point FP32 lines take
+//          16 points and radix 16 (one workgroup of 512 threads either way,
+//          one stage less).
+//   GMAX   lines (planes of one row) a workgroup, where the image has too few
+//          rows to fill the device
+//   TABLE  stage twiddles in a table; beyond 4096 points lookup tables
+//   FITS   the kernels exist: a line and the tables in one workgroup's LDS,
+//          and 16 wavefronts of registers
+//   SUMS   the summing kernel too: its accumulators and steps spill at 1024
+//          threads (8192-point FP64 rows of 8 planes 6.6 ms; unfused 5.3)
+constexpr int row_nt(int real_bytes, int logn) {
+  const int per = real_bytes == 4 && logn == 13 ? 4 : 3;
+  return logn - per < 6 ? 64 : 1 << (logn - per);
+}
+// Wavefronts per SIMD the register budget has to allow (two FP32 workgroups
+// of 512 threads a CU).
+constexpr int row_waves(int real_bytes, int logn) {
+  return real_bytes == 4 && logn >= 9 && logn <= 12 ? 4 : 1;
+}
+template <typename R, int LOGN>
+struct RowShape {
+  static constexpr bool WIDE = sizeof(R) == 4 && LOGN == 13;
+  static constexpr int N = 1 << LOGN;
+  static constexpr int NT = row_nt(sizeof(R), LOGN);
+  static constexpr int GMAX = NT >= 256 ? 1 : 512 / NT;
+  static constexpr bool TABLE = LOGN <= 12;
+  static constexpr int TAB =
+      TABLE ? stage_tw_total(LOGN, WIDE) : kTwLo + (N + kTwLo - 1) / kTwLo;
+  static constexpr bool FITS = LOGN <= 13;
+  static constexpr bool SUMS = FITS && NT <= 512;
+};
+
+// Twiddles of a fused row kernel in s_tab (RowShape::TAB entries).  The
+// input centring is folded into the stage table; lookup tables leave it to
+// the caller (odd elements negated as they are loaded).
+template <typename R, int LOGN>
+__device__ __forceinline__ auto row_twiddles(cplx<R>* s_tab,
+                                             const cplx<R>* tw, R s) {
+  using RS = RowShape<R, LOGN>;
+  if constexpr (RS::TABLE) {
+    fill_stage_twiddles<R, LOGN, RS::WIDE>(s_tab, tw, s, true);
+    return TableTwiddles<R>{s_tab};
+  } else {
+    return load_twiddles(s_tab, s_tab + kTwLo, tw, RS::N);
   }
-  // Add into the image row: all reads first, then all writes.
-  cplx<R>* out = img + (size_t)q * N;
-  cplx<R> old[IT][RAD];
+}
+
+// Row transform of every plane + screen + plane sum into image row q.
+//
+// A workgroup transforms G planes of its row at a time (group gi of NT
+// threads takes planes [gi * per, ...), last to first: Horner's rule,
+// horner_step) and sums the groups' parts in order at the end; G > 1 is for
+// images of few rows, whose serial chain of planes would otherwise leave the
+// device idle.
+//
+// Bound by LDS and vector issue together (a 4096-point FP32 line and plane:
+// ~2200 cycles of LDS exchanges, ~2200 of vector instructions per CU).  The
+// row of the next plane is in flight while one is transformed, the strip
+// marks are bits of a wavefront mask read one plane earlier, and stage twiddles
+// are two-thirds products of table entries (half the LDS reads of a full
+// table).  4096 x 4096 x 32 planes: FP32 1.06 -> 0.96 ms, FP64 2.42 -> 1.96.
+// 8192 points fused: 32 planes of 8192^2 FP32 10.3 (rows, then screen) -> 5.2.
+template <typename R, int LOGN, int G>
+__global__ __launch_bounds__(row_nt(sizeof(R), LOGN) * G, row_waves(sizeof(R), LOGN))
+    void k_row_screen_sum(const cplx<R>* __restrict__ planes,
+                          cplx<R>* __restrict__ img, Geo g,
+                          const cplx<R>* __restrict__ tw,
+                          const uint32_t* __restrict__ strips) {
+  using RS = RowShape<R, LOGN>;
+  constexpr int N = RS::N, NT = RS::NT;
+  constexpr bool WIDE = RS::WIDE;
+  using L = Stage<R, LOGN, 1, NT, stage_npass(LOGN, WIDE) - 1, WIDE>;
+  constexpr int IT = L::IT, RAD = L::RAD, NB = L::NB;
+  __shared__ cplx<R> lds_all[G][lds_line<N>(1)];
+  __shared__ cplx<R> s_tab[RS::TAB];
+  __shared__ cplx<R> s_step[G > 1 ? N : 1];
+  const int q = blockIdx.x;
+  const int gi = G == 1 ? 0 : (int)uniform_u32(threadIdx.x / NT);
+  const int tid = G == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT;
+  cplx<R>* lds = lds_all[gi];
+  const auto twl = row_twiddles<R, LOGN>(s_tab, tw, (R)1);
+  __syncthreads();
+  // The output centring (-1)^p is half a turn in the screen phase (p has the
+  // parity of the thread index: NT and NB are even).
+  static_assert(NT % 2 == 0 && NB % 2 == 0, "output parity per thread");
+  const bool odd = (tid & 1) != 0;
+  const int per = (g.nw + G - 1) / G;
+  const int k0 = gi * per, k1 = min(k0 + per, g.nw);
+  cplx<R> acc[IT][RAD], step[IT][RAD];
+  if constexpr (G > 1) {
+    // Steps of the row's pixels once per workgroup.
+    for (int p = threadIdx.x; p < N; p += NT * G)
+      s_step[p] = screen_step<R>(g, p, q);
+    __syncthreads();
+  }
 #pragma unroll
   for (int it = 0; it < IT; ++it)
 #pragma unroll
     for (int r = 0; r < RAD; ++r) {
-      const int j = threadIdx.x + it * NT;
-      if (NB % NT == 0 || j < NB) old[it][r] = out[j + r * NB];
-    }
-#pragma unroll
-  for (int it = 0; it < IT; ++it)
-#pragma unroll
-    for (int r = 0; r < RAD; ++r) {
-      const int j = threadIdx.x + it * NT;
+      const int j = tid + it * NT, p = j + r * NB;
+      acc[it][r] = {(R)0, (R)0};
+      step[it][r] = {(R)1, (R)0};
       if (NB % NT == 0 || j < NB)
-        out[j + r * NB] = cadd(
-            old[it][r],
-            corrected(g, j + r * NB, q, cmul(sc[it][r].ph, acc[it][r])));
+        step[it][r] = G > 1 ? s_step[G > 1 ? p : 0] : screen_step<R>(g, p, q);
     }
+  using F0 = Stage<R, LOGN, 1, NT, 0, WIDE>;
+  constexpr int IT0 = F0::IT, RAD0 = F0::RAD, NB0 = F0::NB;
+  // Column-strip marks (64-column strips, T = 64) as bits: samples of strips
+  // that hold no data are not read and taken as zero.  The row of the next
+  // plane is requested as the first stage takes the current one from
+  // registers, the marks of the plane after that one plane earlier still.
+  constexpr int MW = (N + 4095) / 4096;
+  constexpr bool kUniform = NB0 % 64 == 0 && NT % 64 == 0;
+  const bool skip = g.T == 64;
+  const int lane = (int)threadIdx.x & 63;
+  const size_t row = (size_t)stack_row(g, q) * N;
+  uint32_t mk[MW];
+  unsigned long long mask[MW];
+  auto load_marks = [&](int n) {
+    const int k = k0 + n;
+    const bool in = n >= 0 && k < k1;
+#pragma unroll
+    for (int w = 0; w < MW; ++w) {
+      mk[w] = in ? 1u : 0u;
+      if (skip && in)
+        mk[w] = strips[(size_t)k * g.tiles_u +
+                       min(w * 64 + lane, g.tiles_u - 1)];
+    }
+  };
+  auto take_marks = [&]() {
+#pragma unroll
+    for (int w = 0; w < MW; ++w) mask[w] = __ballot(mk[w] != 0u);
+  };
+  cplx<R> buf[IT0][RAD0];
+  auto request = [&](int n, int it, int r) {
+    const int j = tid + it * NT;
+    buf[it][r] = {(R)0, (R)0};
+    if (NB0 % NT == 0 || j < NB0) {
+      const int e = j + r * NB0;
+      const int sb = kUniform ? (int)uniform_u32(e >> 6) : e >> 6;
+      if ((mask[MW > 1 ? sb >> 6 : 0] >> (sb & 63)) & 1ull)
+        buf[it][r] = planes[(size_t)(k0 + n) * g.nv * N + row + e];
+    }
+  };
+  load_marks(per - 1);
+  take_marks();
+#pragma unroll
+  for (int it = 0; it < IT0; ++it)
+#pragma unroll
+    for (int r = 0; r < RAD0; ++r) request(per - 1, it, r);
+  load_marks(per - 2);
+  for (int n = per - 1; n >= 0; --n) {
+    take_marks();  // of plane n - 1
+    load_marks(n - 2);
+    auto ld = [&](int e, int, int it, int r) {
+      const cplx<R> v = buf[it][r];
+      request(n - 1, it, r);
+      return RS::TABLE ? v : checker(v, e);
+    };
+    auto st = [&](int, int, int it, int r, cplx<R> v) {
+      acc[it][r] = horner_step(acc[it][r], step[it][r], v);
+    };
+    fft_line<R, LOGN, 1, NT, WIDE>(lds, ld, st, twl, (R)1, tid);
+  }
+  cplx<R>* out = img + (size_t)q * N;
+  if constexpr (G == 1) {
+    // Add into the image row: all reads first, then all writes.
+    cplx<R> old[IT][RAD];
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+      for (int r = 0; r < RAD; ++r) {
+        const int j = tid + it * NT;
+        if (NB % NT == 0 || j < NB) old[it][r] = out[j + r * NB];
+      }
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+      for (int r = 0; r < RAD; ++r) {
+        const int j = tid + it * NT, p = j + r * NB;
+        if (NB % NT == 0 || j < NB)
+          out[p] = cadd(old[it][r],
+                        corrected(g, p, q,
+                                  cmul(screen_at<R>(g, p, q, odd),
+                                       acc[it][r])));
+      }
+  } else {
+    // Group u's part belongs at step^(u per): Horner's rule once more, over
+    // the groups.
+    __syncthreads();  // the last stage's reads are done
+#pragma unroll
+    for (int it = 0; it < IT; ++it)
+#pragma unroll
+      for (int r = 0; r < RAD; ++r) {
+        const int j = tid + it * NT;
+        if (NB % NT == 0 || j < NB) lds[j + r * NB] = acc[it][r];
+      }
+    __syncthreads();
+    for (int p = threadIdx.x; p < N; p += NT * G) {
+      const cplx<R> s1 = s_step[p];
+      cplx<R> sp = s1;
+      for (int i = 1; i < per; ++i) sp = cmul(sp, s1);
+      cplx<R> sum = lds_all[G - 1][p];
+#pragma unroll
+      for (int u = G - 2; u >= 0; --u)
+        sum = horner_step(sum, sp, lds_all[u][p]);
+      out[p] = cadd(out[p],
+                    corrected(g, p, q,
+                              cmul(screen_at<R>(g, p, q, (p & 1) != 0), sum)));
+    }
+  }
 }
 
 // Degridding counterpart: image row q times each plane's conjugate screen,
-// then the row transform (sign -1), written to row q of every plane.
-template <typename R, int LOGN, int NT>
-__global__ __launch_bounds__(NT, sizeof(R) == 4 ? 4 : 1) void k_screen_row_bcast(
-    const void* __restrict__ img, int img_real, cplx<R>* __restrict__ planes,
-    Geo g, const cplx<R>* __restrict__ tw) {
-  constexpr int N = 1 << LOGN;
-  using F0 = Stage<R, LOGN, 1, NT, 0>;
+// then the row transform (sign -1), written to row q of every plane.  The
+// planes are cut into gridDim.y runs, for images of few rows.
+template <typename R, int LOGN>
+__global__ __launch_bounds__(row_nt(sizeof(R), LOGN), row_waves(sizeof(R), LOGN))
+    void k_screen_row_bcast(const void* __restrict__ img, int img_real,
+                            cplx<R>* __restrict__ planes, Geo g,
+                            const cplx<R>* __restrict__ tw) {
+  using RS = RowShape<R, LOGN>;
+  constexpr int N = RS::N, NT = RS::NT;
+  constexpr bool WIDE = RS::WIDE;
+  using F0 = Stage<R, LOGN, 1, NT, 0, WIDE>;
   constexpr int IT = F0::IT, RAD = F0::RAD, NB = F0::NB;
   __shared__ cplx<R> lds[lds_line<N>(1)];
-  __shared__ cplx<R> s_tab[stage_tw_total(LOGN)];
+  __shared__ cplx<R> s_tab[RS::TAB];
   const int q = blockIdx.x;
-  // Stage twiddles in LDS (conjugate: sign -1), the input centring folded
-  // into the last stage; the output centring stays on the stores (the
-  // column transform that follows centres the other axis).
-  fill_stage_twiddles<R, LOGN>(s_tab, tw, (R)-1, true);
+  const auto twl = row_twiddles<R, LOGN>(s_tab, tw, (R)-1);
   __syncthreads();
-  const TableTwiddles<R> twl{s_tab};
-  cplx<R> x[IT][RAD];
-  Screen<R> sc[IT][RAD];
+  const int per = (g.nw + gridDim.y - 1) / gridDim.y;
+  const int k0 = (int)blockIdx.y * per, k1 = min(k0 + per, g.nw);
+  // x: the pixel times the conjugate screen of the next plane.
+  cplx<R> x[IT][RAD], step[IT][RAD];
 #pragma unroll
   for (int it = 0; it < IT; ++it)
 #pragma unroll
     for (int r = 0; r < RAD; ++r) {
       const int j = threadIdx.x + it * NT;
       x[it][r] = {(R)0, (R)0};
+      step[it][r] = {(R)1, (R)0};
       if (NB % NT == 0 || j < NB) {
         const int p = j + r * NB;
+        cplx<R> v = {(R)0, (R)0};
         if (img_real) {
-          x[it][r].re = reinterpret_cast<const R*>(img)[(size_t)q * N + p];
+          v.re = reinterpret_cast<const R*>(img)[(size_t)q * N + p];
         } else {
-          x[it][r] = reinterpret_cast<const cplx<R>*>(img)[(size_t)q * N + p];
+          v = reinterpret_cast<const cplx<R>*>(img)[(size_t)q * N + p];
         }
-        x[it][r] = corrected(g, p, q, x[it][r]);
-        sc[it][r].init(g, p, q, true);
+        // The phasor of plane k0, its phase formed in FP64.
+        const cplx<double> ph = turns_phasor(
+            fma((double)k0, g.dw, g.w0) * n_minus_one(g, p, q));
+        const cplx<R> a = {(R)ph.re, (R)ph.im};
+        const cplx<R> b = screen_step<R>(g, p, q);
+        x[it][r] = cmul(corrected(g, p, q, v), cplx<R>{a.re, -a.im});
+        step[it][r] = {b.re, -b.im};
       }
     }
-  for (int k = 0; k < g.nw; ++k) {
+  for (int k = k0; k < k1; ++k) {
     cplx<R>* line = planes + ((size_t)k * g.nv + q) * N;
-    auto ld = [&](int, int, int it, int r) {
-      const auto w = sc[it][r].next(g, k);
-      return cmul(x[it][r], cplx<R>{(R)w.re, (R)w.im});
+    auto ld = [&](int e, int, int it, int r) {
+      const cplx<R> v = x[it][r];
+      x[it][r] = cmul(v, step[it][r]);
+      return RS::TABLE ? v : checker(v, e);
     };
+    // The output centring stays on the stores (the column transform that
+    // follows centres the other axis).
     auto st = [&](int e, int, int, int, cplx<R> v) { line[e] = checker(v, e); };
-    fft_line<R, LOGN, 1, NT>(lds, ld, st, twl, (R)-1);
+    fft_line<R, LOGN, 1, NT, WIDE>(lds, ld, st, twl, (R)-1);
   }
 }
 
@@ -1153,7 +1361,9 @@ bool rows_t(cplx<R>* data, int64_t nrows, const cplx<R>* tw, R s,
                          tw, s, strips, rows_per_plane, strips_per_row);
       return true;
     }
-    if constexpr (NT % 64 == 0 && ((1 << LOGN) / 8) % 64 == 0) {
+    // Shorter rows are fused with the screen (RowShape).
+    if constexpr (!RowShape<R, LOGN>::SUMS && NT % 64 == 0 &&
+                  ((1 << LOGN) / 8) % 64 == 0) {
       hipLaunchKernelGGL((k_fft_rows<R, LOGN, NT, true>),
                          dim3((unsigned)nrows), dim3(NT), 0, st, data, nrows,
                          tw, s, strips, rows_per_plane, strips_per_row);
@@ -1317,15 +1527,44 @@ bool cols4_t(cplx<R>* data, int ncols, int nplanes, const cplx<R>* tw, R s,
   }
 }
 
+// Wavefronts a launch should have at least, to keep every SIMD of the device
+// (256 CUs of four) busy with a few.
+constexpr int64_t kEnoughWaves = 4096;
+
+template <typename R, int LOGN, int G>
+void row_screen_g(const cplx<R>* planes, cplx<R>* img, const Geo& g,
+                  const cplx<R>* tw, const uint32_t* strips, hipStream_t st) {
+  hipLaunchKernelGGL((k_row_screen_sum<R, LOGN, G>), dim3(g.nv),
+                     dim3(RowShape<R, LOGN>::NT * G), 0, st, planes, img, g,
+                     tw, strips);
+}
+
 template <typename R, int LOGN>
 bool row_screen_t(const cplx<R>* planes, cplx<R>* img, const Geo& g,
                   const cplx<R>* tw, const uint32_t* strips, hipStream_t st) {
-  if constexpr (LOGN > 12) {
+  using RS = RowShape<R, LOGN>;
+  if constexpr (!RS::SUMS) {
     return false;
   } else {
-    constexpr int NT = row_threads(LOGN);
-    hipLaunchKernelGGL((k_row_screen_sum<R, LOGN, NT>), dim3(g.nv), dim3(NT),
-                       0, st, planes, img, g, tw, strips);
+    constexpr int GM = RS::GMAX;
+    const int64_t waves = (int64_t)g.nv * RS::NT / 64;
+    // Half the groups where that fills the device, or the planes run out.
+    if constexpr (GM >= 4) {
+      if (g.nw > 2 && waves * 2 < kEnoughWaves) {
+        if (GM > 4 && (g.nw <= 4 || waves * 4 >= kEnoughWaves))
+          row_screen_g<R, LOGN, 4>(planes, img, g, tw, strips, st);
+        else
+          row_screen_g<R, LOGN, GM>(planes, img, g, tw, strips, st);
+        return true;
+      }
+    }
+    if constexpr (GM >= 2) {
+      if (g.nw > 1 && waves < kEnoughWaves) {
+        row_screen_g<R, LOGN, 2>(planes, img, g, tw, strips, st);
+        return true;
+      }
+    }
+    row_screen_g<R, LOGN, 1>(planes, img, g, tw, strips, st);
     return true;
   }
 }
@@ -1333,12 +1572,16 @@ bool row_screen_t(const cplx<R>* planes, cplx<R>* img, const Geo& g,
 template <typename R, int LOGN>
 bool screen_bcast_t(const void* img, int img_real, cplx<R>* planes,
                     const Geo& g, const cplx<R>* tw, hipStream_t st) {
-  if constexpr (LOGN > 12) {
+  using RS = RowShape<R, LOGN>;
+  if constexpr (!RS::FITS) {
     return false;
   } else {
-    constexpr int NT = row_threads(LOGN);
-    hipLaunchKernelGGL((k_screen_row_bcast<R, LOGN, NT>), dim3(g.nv),
-                       dim3(NT), 0, st, img, img_real, planes, g, tw);
+    int runs = 1;
+    while (runs * 2 <= g.nw &&
+           (int64_t)g.nv * RS::NT / 64 * runs < kEnoughWaves)
+      runs *= 2;
+    hipLaunchKernelGGL((k_screen_row_bcast<R, LOGN>), dim3(g.nv, runs),
+                       dim3(RS::NT), 0, st, img, img_real, planes, g, tw);
     return true;
   }
 }
@@ -1378,13 +1621,19 @@ size_t fft_row_scratch_bytes(int n, int elem_bytes) {
              ? (size_t)kSplitRowGroups * n * elem_bytes : 0;
 }
 
-// The row kernels for n read by strip marks when one wavefront's 64
-// first-stage samples lie in one strip: the one-pass and two-half forms
-// at n >= 1024, not the 4-way split.
+// The plain row transforms read by strip marks when one wavefront's 64
+// first-stage samples lie in one strip: the one-pass and two-half forms of
+// rows too long to be fused, not the 4-way split.
 bool fft_rows_can_mask(int n, int elem_bytes) {
-  return n >= 1024 && fft_supported(n, elem_bytes) &&
+  return fft_supported(n, elem_bytes) && !rows_can_fuse(n, elem_bytes) &&
          !fft_row_needs_scratch(n, elem_bytes);
 }
+
+bool rows_can_fuse(int n, int elem_bytes) {
+  return n <= (elem_bytes == 16 ? 4096 : 8192);
+}
+
+bool rows_can_bcast(int n, int) { return n <= 8192; }
 
 template <typename R>
 bool launch_fft_rows(void* data, int n, int64_t nrows, const void* tw, int sign,

@@ -253,6 +253,10 @@ bool launch_fft_rows(void* data, int n, int64_t nrows, const void* tw,
                      int sign, void* scratch, const uint32_t* strips,
                      int rows_per_plane, hipStream_t st);
 bool fft_rows_can_mask(int n, int elem_bytes);
+// The fused row transform + screen kernels take rows of n points: imaging
+// (with the plane sum), and degridding.
+bool rows_can_fuse(int n, int elem_bytes);
+bool rows_can_bcast(int n, int elem_bytes);
 // Column transforms; with `strips` non-null, the blocks of column strips
 // (strip_w columns of one plane) whose mark is zero are skipped; with
 // `tiles` non-null (per-tile record counts, tile edge strip_w), rows of
