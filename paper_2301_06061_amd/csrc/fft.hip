@@ -671,9 +671,17 @@ __global__ __launch_bounds__(NT) void k_fft_cols_split(
   constexpr int NH = 1 << LOGH;  // half the column length
   constexpr int N = 2 * NH;
   __shared__ cplx<R> lds[lds_line<NH>(BC)];
-  __shared__ cplx<R> s_lo[kTwLo], s_hi[(NH + kTwLo - 1) / kTwLo];
+  // FP32: stage twiddles in a table, radix-16 stages for the longest columns
+  // (one LDS exchange less); FP64 has the registers and LDS for neither.
+  // 4096^2 x 32 planes of the stack, ms: FP32 2.93 -> 2.80, 2048^2 x 16
+  // 0.198 -> 0.188; from the busy-tile store 1.36 -> 1.37 (not used); FP64
+  // with the table 2.71 -> 2.74, with radix 16 (512 threads) 2.78.
+  constexpr bool TABLE = sizeof(R) == 4 && !TS, WIDE = TABLE && LOGH == 11;
+  constexpr int TAB = TABLE ? stage_tw_total(LOGH, WIDE)
+                            : kTwLo + (NH + kTwLo - 1) / kTwLo;
+  __shared__ cplx<R> s_tab[TAB];
   __shared__ cplx<R> f_lo[kTwLo], f_hi[N / kTwLo];
-  using F0 = Stage<R, LOGH, BC, NT, 0>;
+  using F0 = Stage<R, LOGH, BC, NT, 0, WIDE>;
   const int nb_plane = ncols / BC;
   const int nb = nb_plane * nplanes;
   const int L = xcd_block<R, BC>((int)blockIdx.x, nb);
@@ -684,17 +692,18 @@ __global__ __launch_bounds__(NT) void k_fft_cols_split(
       strips[plane * (ncols >> log_strip) + (col0 >> log_strip)] == 0u)
     return;
   cplx<R>* base = data + (size_t)plane * N * ncols + col0;
-  // The loads of the prologue go first (the hardware returns loads in
-  // order): one entry of the four twiddle tables per thread (W_NH^m and
-  // W_NH^(64 m) for the half-length stages, W_N^m and W_N^(64 m) for the
-  // difference terms), and the tile counts.
+  // Without the stage table the prologue's loads go first (the hardware
+  // returns loads in order): one entry of the four twiddle tables per thread
+  // (W_NH^m and W_NH^(64 m) for the half-length stages, W_N^m and W_N^(64 m)
+  // for the difference terms), then the tile counts.
   static_assert(NT >= 4 * kTwLo && N / kTwLo <= kTwLo, "one entry a thread");
   const int tq = min((int)threadIdx.x / kTwLo, 3), tm = threadIdx.x % kTwLo;
   const int tidx = tq == 0   ? 2 * tm
                    : tq == 1 ? tm
                    : tq == 2 ? 2 * kTwLo * min(tm, NH / kTwLo - 1)
                              : kTwLo * min(tm, N / kTwLo - 1);
-  const cplx<R> tval = tw[tidx];
+  cplx<R> tval;
+  if constexpr (!TABLE) tval = tw[tidx];
   TileRows tr(tiles, plane, N, ncols, col0, log_strip, base);
   // TS: lane l holds the store slot of tile row l of this strip (any
   // value where the tile has no records: such rows are never read).
@@ -705,15 +714,16 @@ __global__ __launch_bounds__(NT) void k_fft_cols_split(
     myslot = (int)tslot[((size_t)plane * rows + min(lane, rows - 1)) * tcols +
                         (col0 >> log_strip)];
   }
-  if (threadIdx.x < 4 * kTwLo) {
-    if (tq == 0) s_lo[tm] = tval;
-    else if (tq == 1) f_lo[tm] = tval;
-    else if (tq == 2) { if (tm < NH / kTwLo) s_hi[tm] = tval; }
-    else if (tm < N / kTwLo) f_hi[tm] = tval;
+  if constexpr (!TABLE) {
+    if (threadIdx.x < 4 * kTwLo) {
+      if (tq == 0) s_tab[tm] = tval;
+      else if (tq == 1) f_lo[tm] = tval;
+      else if (tq == 2) { if (tm < NH / kTwLo) s_tab[kTwLo + tm] = tval; }
+      else if (tm < N / kTwLo) f_hi[tm] = tval;
+    }
+    __syncthreads();
   }
   tr.finish();
-  const Twiddles<R> twl{s_lo, s_hi}, twf{f_lo, f_hi};
-  __syncthreads();
   cplx<R> diff[F0::IT][F0::RAD];
   // The first stage takes the thread's sample pairs in order n = it * RAD +
   // r; the pair n + AHEAD is requested when pair n is combined, so each
@@ -778,6 +788,21 @@ __global__ __launch_bounds__(NT) void k_fft_cols_split(
   };
 #pragma unroll
   for (int n = 0; n < AHEAD && n < NE; ++n) issue(n);
+  const auto twl = [&] {
+    if constexpr (TABLE) {
+      // The tables, while the first samples are in flight.
+      for (int i = threadIdx.x; i < kTwLo + N / kTwLo; i += NT) {
+        if (i < kTwLo) f_lo[i] = tw[i];
+        else f_hi[i - kTwLo] = tw[(i - kTwLo) * kTwLo];
+      }
+      fill_stage_twiddles<R, LOGH, WIDE>(s_tab, tw, s, false, 2);
+      __syncthreads();
+      return TableTwiddles<R>{s_tab};
+    } else {
+      return Twiddles<R>{s_tab, s_tab + kTwLo};
+    }
+  }();
+  const Twiddles<R> twf{f_lo, f_hi};
   auto ld_sum = [&](int e, int, int it, int r) {
     const int n = it * F0::RAD + r;
     if (n + AHEAD < NE) issue(n + AHEAD);
@@ -790,12 +815,12 @@ __global__ __launch_bounds__(NT) void k_fft_cols_split(
   auto st_even = [&](int e, int c, int, int, cplx<R> v) {
     base[(size_t)(2 * e) * ncols + c] = v;
   };
-  fft_line<R, LOGH, BC, NT>(lds, ld_sum, st_even, twl, s);
+  fft_line<R, LOGH, BC, NT, WIDE>(lds, ld_sum, st_even, twl, s);
   auto ld_diff = [&](int, int, int it, int r) { return diff[it][r]; };
   auto st_odd = [&](int e, int c, int, int, cplx<R> v) {
     base[(size_t)(2 * e + 1) * ncols + c] = cplx<R>{-v.re, -v.im};
   };
-  fft_line<R, LOGH, BC, NT>(lds, ld_diff, st_odd, twl, s);
+  fft_line<R, LOGH, BC, NT, WIDE>(lds, ld_diff, st_odd, twl, s);
 }
 
 // ---- four-step column transform for long columns (N = N1 * N2) ---------
