@@ -76,7 +76,7 @@ struct Layout {
   int64_t tstore_slots;
   // workspace offsets
   size_t o_tw_u, o_tw_v, o_corr, o_counts, o_sums, o_keyrank, o_rec, o_chunks,
-      o_slot, o_counters, o_split, o_extra, o_busy, o_idle, o_copies, o_desc,
+      o_slot, o_counters, o_split, o_busy, o_idle, o_copies, o_desc,
       o_strips, o_partials, o_scratch, o_rowscratch, o_clean, o_p_hist1, o_p_hist1x,
       o_p_btot, o_p_bounds, o_p_seg, o_p_rec1, o_p_keys, o_p_chunk0, o_p_rank2,
       o_p_hist2, o_p_hist2x, o_tstore, o_tslot, o_zero, total;
@@ -291,7 +291,6 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
   L->o_slot = take((size_t)L->ntiles * 4);
   L->o_counters = take(64);
   L->o_split = take((size_t)(L->max_slots / 2 + 1) * 4);
-  L->o_extra = take((size_t)L->max_extra * 8);
   L->o_busy = take((size_t)L->ntiles * 4);
   // One descriptor per gridding work item (every tile, every extra chunk).
   L->o_desc = take((size_t)(L->ntiles + L->max_extra + 1) * kDescWords * 4);
@@ -497,7 +496,6 @@ ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
   tw.tile_slot = slot;
   tw.counters = counters;
   tw.split_list = split;
-  tw.extra = pl->w<uint2>(L.o_extra);
   tw.busy = pl->w<uint32_t>(L.o_busy);
   tw.idle = pl->w<uint32_t>(L.o_idle);
   tw.strips = strips;
@@ -590,7 +588,6 @@ GridJob<R> make_job(ws_plan* pl, int accumulate, bool ts = false) {
   j.pitch = grid_lds_pitch(L.T, pl->p.support);
   j.offsets = pl->w<uint32_t>(L.o_counts);
   j.counters = pl->w<uint32_t>(L.o_counters);
-  j.extra = pl->w<uint2>(L.o_extra);
   j.busy = pl->w<uint32_t>(L.o_busy);
   j.idle = pl->w<uint32_t>(L.o_idle);
   j.tile_chunks = pl->w<uint32_t>(L.o_chunks);
@@ -787,13 +784,10 @@ ws_status degrid_impl(ws_plan* pl, const void* image, int image_is_real,
   WS_TRY(bin_records<R>(pl, m, flat_source(uvw, nullptr, weight), 1,
                         nullptr, &max_items, nullptr, false, vis_out));
   WS_TRY(launch(pl, "degrid_tiles", [&] {
-    launch_degrid_tiles<R>(g, pl->w<uint32_t>(L.o_counts),
-                           pl->w<uint32_t>(L.o_counters),
-                           pl->w<uint2>(L.o_extra),
-                           pl->w<uint32_t>(L.o_busy), pl->planes,
-                           pl->work + L.o_rec,
-                           L.chunk, vis_out, max_items, pl->cus,
-                           pl->stream);
+    launch_degrid_tiles<R>(g, pl->w<uint32_t>(L.o_counters),
+                           pl->w<uint32_t>(L.o_desc),
+                           max_items - (uint32_t)L.ntiles, pl->planes,
+                           pl->work + L.o_rec, vis_out, pl->stream);
   }));
   return WS_OK;
 }

@@ -371,8 +371,8 @@ __device__ __forceinline__ TileRecords tile_records(const Geo& g, int t,
   TileRecords r;
   r.work = 0;
   if (mode_degrid) {
-    r.work = off[(uint32_t)t * kRegions + kRegions] -
-             off[(uint32_t)t * kRegions];
+    r.first[0] = off[(uint32_t)t * kRegions];
+    r.work = off[(uint32_t)t * kRegions + kRegions] - r.first[0];
     return r;
   }
   uint32_t lo[kSegments], hi[kSegments];
@@ -430,8 +430,13 @@ __device__ __forceinline__ void emit_tile(const Geo& g, const TileWork& w,
   w.tile_slot[t] = slot;
   w.tile_chunks[t] = nch;
   if (w.degrid) {
-    for (uint32_t c = 1; c < nch; ++c)
-      w.extra[e0 + c - 1] = make_uint2((uint32_t)t, c);
+    const uint32_t end = r.first[0] + r.work;
+    for (uint32_t c = 0; c < nch; ++c) {
+      const uint32_t b = r.first[0] + c * w.chunk;
+      const size_t n = c == 0 ? (size_t)at : (size_t)g.ntiles + e0 + c - 1;
+      reinterpret_cast<uint4*>(w.desc)[n] = make_uint4(
+          (uint32_t)t, b, nch == 1 ? end : min(end, b + w.chunk), 0u);
+    }
     return;
   }
   // Descriptors (layout: kDescWords in ws_kernels.h).

@@ -27,10 +27,9 @@
 // tile with records, then groups of tiles without records, which only get
 // zeros.
 //
-// Degridding: one workgroup per (tile, chunk) item (the hardware overlaps
-// the latencies of the workgroups resident on a CU); each loads the
-// transformed plane's tile plus an h-cell halo into LDS in one round trip,
-// and each lane evaluates one visibility's K x K weighted sum from LDS.
+// Degridding: one workgroup per (tile, chunk) item; tiles of a few records
+// are read from the transformed plane directly, denser ones staged in LDS with
+// an h-cell halo (k_degrid_tiles).
 #include "ws_kernels.h"
 
 namespace ws {
@@ -80,32 +79,10 @@ __device__ __forceinline__ double kern1(const Geo& g, double d) {
   }
 }
 
-struct Item {
-  int tile;
-  uint32_t chunk;  // chunk of the tile
-};
-
 // Work items of one plan, in queue order: the further chunks of split
 // (hot) tiles, then the first chunk of every tile that has records.
 __device__ __forceinline__ uint32_t item_total(const uint32_t* counters) {
   return counters[2] + counters[4];
-}
-
-__device__ __forceinline__ Item resolve_item(uint32_t item,
-                                             const uint32_t* counters,
-                                             const uint2* extra,
-                                             const uint32_t* busy) {
-  const uint32_t nextra = counters[2];
-  Item it;
-  if (item < nextra) {
-    const uint2 tc = extra[item];
-    it.tile = (int)tc.x;
-    it.chunk = tc.y;
-  } else {
-    it.tile = (int)busy[item - nextra];
-    it.chunk = 0;
-  }
-  return it;
 }
 
 __device__ __forceinline__ void tile_origin(const Geo& g, int t, int& k,
@@ -178,6 +155,11 @@ __device__ __forceinline__ void zero_tile(int T, cplx<R>* dst,
 
 __device__ __forceinline__ uint32_t uniform(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
+}
+
+// Index of this wavefront in its workgroup, as a scalar.
+__device__ __forceinline__ int wave_index() {
+  return (int)uniform(threadIdx.x >> 6);
 }
 
 template <typename R>
@@ -684,13 +666,50 @@ __global__ __launch_bounds__(kMergeCells* kMergeRuns) void k_grid_merge(
   }
 }
 
+// Row of the stack that holds column frequency q, for power-of-two step
+// lengths (stack_row without its divisions).
+__device__ __forceinline__ int stack_row_fast(const Geo& g, int q) {
+  if (g.perm_n1 == 0) return q;
+  const int l1 = 31 - __clz(g.perm_n1), l2 = 31 - __clz(g.perm_n2);
+  return ((q & (g.perm_n1 - 1)) << l2) + (q >> l1);
+}
+
+// Degridding.  One workgroup per item (descriptor: tile and its record
+// range), the extra chunks of large tiles first; blocks past the item counts
+// exit.  Runs of kDegridRun items go to one XCD (blocks are dealt to the
+// eight XCDs in turn), so that neighbouring tiles share their halo in its L2.
+//
+// Bound by the tiles' loads and their latency: a 64 x 64 FP32 tile with its
+// halo is 39 KB, four workgroups a CU.  Tiles of at most kDegridDirect records
+// do not load it: K lanes take one record each (one kernel row a lane) and
+// read its cells from the stack, about 1 KB a record.  Denser tiles are
+// staged in LDS, aligned rows of T cells two (FP32) a load and the 2 H halo
+// columns apart, with the first records in flight behind them; then one record
+// a lane.  4096^2 x 32 planes, 1e7 visibilities: 1.62 -> 0.65 ms.
+constexpr int kDegridRun = 64;
+constexpr uint32_t kDegridDirect = 32;
+
+// Sum over the K lanes of a record's group (rows 0 .. K-1), valid on row 0.
+template <typename R, int K>
+__device__ __forceinline__ R row_sum(R v, int row) {
+  constexpr int P = K > 8 ? 8 : (K > 4 ? 4 : (K > 2 ? 2 : 1));
+  int len = K;
+#pragma unroll
+  for (int o = P; o > 0; o >>= 1) {
+    if (K > 1) {
+      const R t = __shfl(v, ((int)threadIdx.x & 63) + o, 64);
+      if (row + o < len) v += t;
+      len = o;
+    }
+  }
+  return v;
+}
+
 template <typename R, int K, int KT>
 __global__ __launch_bounds__(256) void k_degrid_tiles(
-    Geo g, const uint32_t* __restrict__ offsets,
-    uint32_t* __restrict__ counters, const uint2* __restrict__ extra,
-    const uint32_t* __restrict__ busy,
+    Geo g, const uint32_t* __restrict__ counters,
+    const uint4* __restrict__ desc, uint32_t extra_blocks,
     const cplx<R>* __restrict__ planes, const Record<R>* __restrict__ rec,
-    uint32_t chunk,
     cplx<R>* __restrict__ vis_out) {
   constexpr int H = (K - 1) / 2;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -698,78 +717,175 @@ __global__ __launch_bounds__(256) void k_degrid_tiles(
   const int T = g.T;
   const int W = T + 2 * H;
   const R cn = (R)g.cnorm;
-  // One workgroup per item (the hardware overlaps the latencies of the
-  // workgroups resident on a CU); blocks past the item count exit.
+  uint4 d;
+  if (blockIdx.x < extra_blocks) {
+    d = desc[(size_t)g.ntiles + blockIdx.x];
+    if (blockIdx.x >= counters[2]) return;
+  } else {
+    const uint32_t b = blockIdx.x - extra_blocks;
+    const uint32_t x = b % 8u, n = b / 8u;
+    const uint32_t item =
+        ((n / kDegridRun) * 8u + x) * kDegridRun + n % kDegridRun;
+    if (item >= (uint32_t)g.ntiles) return;
+    d = desc[item];
+    if (item >= counters[4]) return;
+  }
+  const uint32_t start = d.y, end = d.z;
+  int k, oy, ox;
+  tile_origin(g, (int)d.x, k, oy, ox);
+  const cplx<R>* src = planes + (size_t)k * g.nv * g.nu;
+  const int lane = (int)threadIdx.x & 63, wave = wave_index();
+  if (end - start <= kDegridDirect) {
+    using RL = RowLanes<K>;
+    const int slot = lane / K, row = lane - slot * K;
+    const bool act = slot < RL::RPW;
+    for (uint32_t r0 = start + (uint32_t)wave * RL::RPW; r0 < end;
+         r0 += 4u * RL::RPW) {
+      const uint32_t r = r0 + (uint32_t)slot;
+      const bool on = act && r < end;
+      const Record<R> q = rec[on ? r : start];
+      const int i0 = cell_i(q.cell) - H, gr = cell_j(q.cell) + row - H;
+      const bool in = on && (unsigned)gr < (unsigned)g.nv;
+      const cplx<R>* line =
+          src + (size_t)stack_row_fast(g, in ? gr : 0) * g.nu;
+      cplx<R> v[K];
+#pragma unroll
+      for (int a = 0; a < K; ++a) {
+        const int gc = min(max(i0 + a, 0), g.nu - 1);
+        v[a] = line[gc];
+      }
+      cplx<R> acc = {(R)0, (R)0};
+#pragma unroll
+      for (int a = 0; a < K; ++a) {
+        const R gx = kern1<KT>(g, (R)(a - H) - q.dx);
+        const bool c = in && (unsigned)(i0 + a) < (unsigned)g.nu;
+        acc.re += gx * (c ? v[a].re : (R)0);
+        acc.im += gx * (c ? v[a].im : (R)0);
+      }
+      const R gy = kern1<KT>(g, (R)(row - H) - q.dy);
+      acc.re = row_sum<R, K>(gy * acc.re, row);
+      acc.im = row_sum<R, K>(gy * acc.im, row);
+      if (on && row == 0)
+        vis_out[q.idx] = cplx<R>{cn * q.vr * acc.re, cn * q.vr * acc.im};
+    }
+    return;
+  }
+  // First records, then the tile, all in flight together.
+  constexpr int kRec = sizeof(R) == 4 ? 4 : 2;
+  const uint32_t step = blockDim.x;
+  auto load = [&](uint32_t r0, Record<R> (&q)[kRec]) {
+#pragma unroll
+    for (int u = 0; u < kRec; ++u) {
+      const uint32_t r = r0 + (uint32_t)u * step;
+      q[u] = rec[r < end ? r : end - 1];
+    }
+  };
+  Record<R> cur[kRec];
+  uint32_t rb = start + threadIdx.x;
+  load(rb, cur);
+  // Tile rows -H .. T + H - 1 of the plane, columns [ox, ox + T): V cells a
+  // load; then the 2 H halo columns.  Addresses are clamped into the plane,
+  // so the loads are unconditional; cells off the grid are zero.
   {
-    const uint32_t item = blockIdx.x;
-    if (item >= item_total(counters)) return;
-    const Item it = resolve_item(item, counters, extra, busy);
-    const int t = it.tile;
-    const uint32_t c = it.chunk;
-    int k, oy, ox;
-    tile_origin(g, t, k, oy, ox);
-    const uint32_t r0 = offsets[(uint32_t)t * kRegions];
-    const uint32_t r1 = offsets[(uint32_t)t * kRegions + kRegions];
-    const uint32_t start = r0 + c * chunk;
-    if (start >= r1) return;
-    const uint32_t end = r1 - start > chunk ? start + chunk : r1;
-    const cplx<R>* src = planes + (size_t)k * g.nv * g.nu;
-    // Tile + halo into LDS, up to kTile loads in flight per thread before
-    // their LDS writes (one round trip for a 64 x 64 tile with K <= 15;
-    // addresses clamped into the plane, so the loads are unconditional;
-    // cells off the grid are zeroed afterwards).
-    constexpr int kTile = 24;
-    for (int i0 = threadIdx.x; i0 < W * W; i0 += kTile * (int)blockDim.x) {
-      cplx<R> v[kTile];
+    constexpr int V = 16 / (int)sizeof(cplx<R>);
+    struct alignas(16) Vec { cplx<R> c[V]; };
+    constexpr int kTile = sizeof(R) == 4 ? 10 : 18;  // loads in flight
+    const int lt = 31 - __clz(T / V);
+    const int n = W << lt;
+    for (int i0 = threadIdx.x; i0 < n; i0 += kTile * 256) {
+      Vec v[kTile];
 #pragma unroll
       for (int u = 0; u < kTile; ++u) {
-        const int i = i0 + u * (int)blockDim.x;
-        const int ii = i < W * W ? i : W * W - 1;
-        const int lr = ii / W, lc = ii - lr * W;
-        const int gr = oy - H + lr, gc = ox - H + lc;
-        const int grc = gr < 0 ? 0 : (gr >= g.nv ? g.nv - 1 : gr);
-        const int gcc = gc < 0 ? 0 : (gc >= g.nu ? g.nu - 1 : gc);
-        v[u] = src[(size_t)stack_row(g, grc) * g.nu + gcc];
-        if (gr != grc || gc != gcc) v[u] = cplx<R>{(R)0, (R)0};
+        const int i = min(i0 + u * 256, n - 1);
+        const int gr = oy - H + (i >> lt);
+        const int grc = min(max(gr, 0), g.nv - 1);
+        const int lc = (i & ((1 << lt) - 1)) * V;
+        v[u] = *reinterpret_cast<const Vec*>(
+            src + (size_t)stack_row_fast(g, grc) * g.nu + ox + lc);
+        if (gr != grc) {
+#pragma unroll
+          for (int e = 0; e < V; ++e) v[u].c[e] = cplx<R>{(R)0, (R)0};
+        }
       }
 #pragma unroll
       for (int u = 0; u < kTile; ++u) {
-        const int i = i0 + u * (int)blockDim.x;
-        if (i < W * W) s_q[i] = v[u];
+        const int i = i0 + u * 256;
+        if (i < n) {
+          cplx<R>* p =
+              s_q + (i >> lt) * W + H + (i & ((1 << lt) - 1)) * V;
+#pragma unroll
+          for (int e = 0; e < V; ++e) p[e] = v[u].c[e];
+        }
       }
     }
-    lds_barrier();
-    // Records kRec at a time per thread, the next kRec in flight while the
-    // current ones are evaluated (positions past the end re-read the last
-    // record and are not written).
-    constexpr int kRec = sizeof(R) == 4 ? 4 : 2;
-    const uint32_t step = blockDim.x;
-    auto load = [&](uint32_t r0, Record<R> (&q)[kRec]) {
+    if constexpr (H > 0) {
+      const int nh = W * 2 * H;
+      constexpr int kHalo = 3;
+      for (int i0 = threadIdx.x; i0 < nh; i0 += kHalo * 256) {
+        cplx<R> v[kHalo];
 #pragma unroll
-      for (int u = 0; u < kRec; ++u) {
-        const uint32_t r = r0 + (uint32_t)u * step;
-        q[u] = rec[r < end ? r : end - 1];
-      }
-    };
-    Record<R> cur[kRec];
-    uint32_t rb = start + threadIdx.x;
-    load(rb, cur);
-    while (rb < end) {
-      Record<R> nxt[kRec];
-      const uint32_t rn = rb + (uint32_t)kRec * step;
-      load(rn, nxt);
-#pragma unroll
-      for (int u = 0; u < kRec; ++u) {
-        const Record<R>& q = cur[u];
-        const int li = cell_i(q.cell) - ox + H;
-        const int lj = cell_j(q.cell) - oy + H;
-        R gx[K], gy[K];
-#pragma unroll
-        for (int a = 0; a < K; ++a) {
-          gx[a] = kern1<KT>(g, (R)(a - H) - q.dx);
-          gy[a] = kern1<KT>(g, (R)(a - H) - q.dy);
+        for (int u = 0; u < kHalo; ++u) {
+          const int i = min(i0 + u * 256, nh - 1);
+          const int lr = i / (2 * H), h = i - lr * 2 * H;
+          const int gr = oy - H + lr;
+          const int gc = h < H ? ox - H + h : ox + T + h - H;
+          const int grc = min(max(gr, 0), g.nv - 1);
+          const int gcc = min(max(gc, 0), g.nu - 1);
+          v[u] = src[(size_t)stack_row_fast(g, grc) * g.nu + gcc];
+          if (gr != grc || gc != gcc) v[u] = cplx<R>{(R)0, (R)0};
         }
-        cplx<R> acc = {(R)0, (R)0};
+#pragma unroll
+        for (int u = 0; u < kHalo; ++u) {
+          const int i = i0 + u * 256;
+          if (i < nh) {
+            const int lr = i / (2 * H), h = i - lr * 2 * H;
+            s_q[lr * W + (h < H ? h : T + h)] = v[u];
+          }
+        }
+      }
+    }
+  }
+  lds_barrier();
+  // Records kRec at a time per thread, the next kRec in flight while the
+  // current ones are evaluated (positions past the end re-read the last
+  // record and are not written; wavefronts with none skip the evaluation).
+  const uint32_t wb = start + (uint32_t)wave * 64u;
+  for (uint32_t done = 0; wb + done < end; done += (uint32_t)kRec * step) {
+    Record<R> nxt[kRec];
+    const uint32_t rn = rb + (uint32_t)kRec * step;
+    load(rn, nxt);
+#pragma unroll
+    for (int u = 0; u < kRec; ++u) {
+      if (wb + done + (uint32_t)u * step >= end) break;
+      const Record<R>& q = cur[u];
+      const int li = cell_i(q.cell) - ox + H;
+      const int lj = cell_j(q.cell) - oy + H;
+      R gx[K], gy[K];
+#pragma unroll
+      for (int a = 0; a < K; ++a) {
+        gx[a] = kern1<KT>(g, (R)(a - H) - q.dx);
+        gy[a] = kern1<KT>(g, (R)(a - H) - q.dy);
+      }
+      cplx<R> acc = {(R)0, (R)0};
+      // The footprint lies in the staged cells unless the nearest cell is
+      // off the grid.
+      const bool whole = (unsigned)(li - H) < (unsigned)T &&
+                         (unsigned)(lj - H) < (unsigned)T;
+      if (__all(whole)) {
+        const cplx<R>* p = s_q + (lj - H) * W + (li - H);
+#pragma unroll
+        for (int b = 0; b < K; ++b) {
+          cplx<R> racc = {(R)0, (R)0};
+#pragma unroll
+          for (int a = 0; a < K; ++a) {
+            racc.re += gx[a] * p[a].re;
+            racc.im += gx[a] * p[a].im;
+          }
+          acc.re += gy[b] * racc.re;
+          acc.im += gy[b] * racc.im;
+          p += W;
+        }
+      } else {
 #pragma unroll
         for (int b = 0; b < K; ++b) {
           const int row = lj + b - H;
@@ -787,13 +903,13 @@ __global__ __launch_bounds__(256) void k_degrid_tiles(
           acc.re += gy[b] * racc.re;
           acc.im += gy[b] * racc.im;
         }
-        if (rb + (uint32_t)u * step < end)
-          vis_out[q.idx] = cplx<R>{cn * q.vr * acc.re, cn * q.vr * acc.im};
       }
-#pragma unroll
-      for (int u = 0; u < kRec; ++u) cur[u] = nxt[u];
-      rb = rn;
+      if (rb + (uint32_t)u * step < end)
+        vis_out[q.idx] = cplx<R>{cn * q.vr * acc.re, cn * q.vr * acc.im};
     }
+#pragma unroll
+    for (int u = 0; u < kRec; ++u) cur[u] = nxt[u];
+    rb = rn;
   }
 }
 
@@ -829,17 +945,18 @@ void grid_batch_k(const GridJob<R>* jobs, int njobs, size_t lds,
 }
 
 template <typename R, int K, int KT>
-void degrid_k(const Geo& g, const uint32_t* offsets, uint32_t* counters,
-              const uint2* extra, const uint32_t* busy, const void* planes,
-              const void* records, uint32_t chunk,
-              void* vis_out, uint32_t max_items, int cus, hipStream_t st) {
+void degrid_k(const Geo& g, const uint32_t* counters, const uint32_t* desc,
+              uint32_t max_extra, const void* planes, const void* records,
+              void* vis_out, hipStream_t st) {
   const int W = g.T + (K - 1);
   const size_t lds = (size_t)W * W * sizeof(cplx<R>);
-  hipLaunchKernelGGL((k_degrid_tiles<R, K, KT>),
-                     dim3(max_items > 0 ? max_items : 1), dim3(256),
-                     lds, st, g, offsets, counters, extra, busy,
-                     (const cplx<R>*)planes, (const Record<R>*)records,
-                     chunk, (cplx<R>*)vis_out);
+  // Blocks for every tile, whole runs on every XCD.
+  const uint32_t per = 8u * kDegridRun;
+  const uint32_t tiles = ((uint32_t)g.ntiles + per - 1) / per * per;
+  hipLaunchKernelGGL((k_degrid_tiles<R, K, KT>), dim3(max_extra + tiles),
+                     dim3(256), lds, st, g, counters, (const uint4*)desc,
+                     max_extra, (const cplx<R>*)planes,
+                     (const Record<R>*)records, (cplx<R>*)vis_out);
 }
 
 }  // namespace
@@ -926,16 +1043,13 @@ void launch_grid_merge(const Geo& g, const uint32_t* counters,
 }
 
 template <typename R>
-void launch_degrid_tiles(const Geo& g, const uint32_t* offsets,
-                         uint32_t* counters, const uint2* extra,
-                         const uint32_t* busy, const void* planes,
-                         const void* records, uint32_t chunk,
-                         void* vis_out, uint32_t max_items, int cus,
-                         hipStream_t st) {
-  WS_K_SWITCH(g.K, g.kern, (degrid_k<R, KK, KT>(g, offsets, counters,
-                                                extra, busy, planes, records,
-                                                chunk, vis_out, max_items,
-                                                cus, st)));
+void launch_degrid_tiles(const Geo& g, const uint32_t* counters,
+                         const uint32_t* desc, uint32_t max_extra,
+                         const void* planes, const void* records,
+                         void* vis_out, hipStream_t st) {
+  WS_K_SWITCH(g.K, g.kern,
+              (degrid_k<R, KK, KT>(g, counters, desc, max_extra, planes,
+                                   records, vis_out, st)));
 }
 
 #undef WS_K_SWITCH
@@ -963,9 +1077,8 @@ size_t degrid_lds_bytes(int T, int K, int elem_bytes) {
                                      const uint32_t*, uint32_t,            \
                                      hipStream_t);                         \
   template void launch_degrid_tiles<R>(                                    \
-      const Geo&, const uint32_t*, uint32_t*, const uint2*,                \
-      const uint32_t*, const void*, const void*, uint32_t, void*,          \
-      uint32_t, int, hipStream_t);
+      const Geo&, const uint32_t*, const uint32_t*, uint32_t, const void*, \
+      const void*, void*, hipStream_t);
 WS_INST(float)
 WS_INST(double)
 #undef WS_INST

@@ -106,10 +106,11 @@ void launch_bin_scatter(const Geo& g, const VisSource& src, int64_t m,
                         uint32_t nkeys, void* records, int degrid,
                         void* vis_out, hipStream_t st);
 // Everything the tile work pass writes: per tile its chunk count and first
-// scratch slot; the busy, idle, split and extra-chunk lists with their
-// counters; strip marks (or null); busy-list index of every tile with
-// records (tslot, or null); gridding: one descriptor per work item, the
-// first chunk of busy tile i at i, extra item e at ntiles + e.
+// scratch slot; the busy, idle and split lists with their counters; strip
+// marks (or null); busy-list index of every tile with records (tslot, or
+// null); one descriptor per work item, the first chunk of busy tile i at i,
+// extra item e at ntiles + e (gridding: kDescWords words; degridding: four,
+// the tile and its first and end record).
 struct TileWork {
   int degrid;
   uint32_t chunk;  // records per work item
@@ -118,7 +119,6 @@ struct TileWork {
   uint32_t* tile_slot;
   uint32_t* counters;
   uint32_t* split_list;
-  uint2* extra;
   uint32_t* busy;
   uint32_t* idle;
   uint32_t* strips;
@@ -173,7 +173,6 @@ struct GridJob {
   const uint32_t* offsets;    // record offset of every key (+ total)
   uint32_t* counters;         // [1] split tiles, [2] extra items, [3] queue,
                               // [4] busy tiles, [5] idle tiles
-  const uint2* extra;         // (tile, chunk) of the further chunks
   const uint32_t* busy;       // tiles with records ([4] of them)
   const uint32_t* idle;       // tiles without ([5]), zeroed separately
   const uint32_t* tile_chunks;
@@ -231,13 +230,12 @@ void launch_grid_merge(const Geo& g, const uint32_t* counters,
                        void* planes, int accumulate, uint32_t max_split,
                        void* tstore, const uint32_t* tslot, uint32_t tcap,
                        hipStream_t st);
+// max_extra: bound of the extra items (blocks launched for them).
 template <typename R>
-void launch_degrid_tiles(const Geo& g, const uint32_t* offsets,
-                         uint32_t* counters, const uint2* extra,
-                         const uint32_t* busy, const void* planes,
-                         const void* records, uint32_t chunk,
-                         void* vis_out, uint32_t max_items, int cus,
-                         hipStream_t st);
+void launch_degrid_tiles(const Geo& g, const uint32_t* counters,
+                         const uint32_t* desc, uint32_t max_extra,
+                         const void* planes, const void* records,
+                         void* vis_out, hipStream_t st);
 
 // FFT and screen (fft.hip)
 bool fft_supported(int n, int elem_bytes);
