@@ -459,21 +459,52 @@ __device__ __forceinline__ void clear_lds(A* s, uint32_t words) {
   for (uint32_t i = threadIdx.x; i < words; i += blockDim.x) s[i] = (A)0;
 }
 
-// Persistent loop over the items of a queue.  Thread 0 pops queue numbers
-// into s_next; `locate(n, job)` turns number n into its job and the index
-// of the item in that job (returns false past the end).  Queue numbers are
-// popped two items ahead: the descriptor of the item after the current one
+// Queue of the persistent gridders, kept by thread 0 of each workgroup.  All
+// workgroups pop one counter, and atomics on one address run one after the
+// other, 11.5 ns each on this part: popping 91 000 items one by one bounds a
+// launch from below at 1.05 ms.  A pop therefore takes kPopItems items, one from each
+// of as many equal stretches of the queue (its front holds the longest
+// items); the last kPopTail items per workgroup go one by one, for balance.
+// Those 91 000 items (4096^2 x 32 planes, uniform) 1.36 -> 1.33 ms; 8192^2 x
+// 32, K = 9, 3.01 -> 2.96; 2048^2 x 16 0.246 -> 0.228; 1024^2 x 16 unchanged
+// (0.134).  8 and 16 items a pop leave the ends of smaller launches unbalanced.
+constexpr uint32_t kPopItems = 4;
+constexpr uint32_t kPopTail = 4;
+struct Popper {
+  uint32_t* queue;
+  uint32_t groups;  // pops of kPopItems items
+  uint32_t base, taken;
+  __device__ __forceinline__ Popper(uint32_t* q, uint32_t total)
+      : queue(q), base(0), taken(kPopItems) {
+    const uint32_t tail = kPopTail * gridDim.x;
+    groups = total > tail ? (total - tail) / kPopItems : 0u;
+  }
+  __device__ __forceinline__ uint32_t next() {
+    if (taken == kPopItems) {
+      base = atomicAdd(queue, 1u);
+      if (base >= groups) return base + groups * (kPopItems - 1u);
+      taken = 0;
+    }
+    return base + groups * taken++;
+  }
+};
+
+// Persistent loop over the items of a queue of `total`.  Thread 0 pops queue
+// numbers into s_next; `locate(n, job)` turns number n into its job and the
+// index of the item in that job (returns false past the end).  Queue numbers
+// are popped two items ahead: the descriptor of the item after the current one
 // is loaded while the current one accumulates, and that item's first
 // records are requested before the current tile's global stores, which
 // then drain while it starts.  The barriers order LDS only.
 template <typename R, int K, int KT, class Locate>
 __device__ __forceinline__ void item_loop(GridAcc<R>* s_lds, uint32_t* queue,
-                                          uint32_t* s_next,
+                                          uint32_t total, uint32_t* s_next,
                                           const GridJob<R>* job0,
                                           Locate locate) {
+  Popper pop(queue, total);
   if (threadIdx.x == 0) {
-    s_next[0] = atomicAdd(queue, 1u);
-    s_next[1] = atomicAdd(queue, 1u);
+    s_next[0] = pop.next();
+    s_next[1] = pop.next();
   }
   lds_barrier();
   const GridJob<R>* job = job0;
@@ -485,7 +516,7 @@ __device__ __forceinline__ void item_loop(GridAcc<R>* s_lds, uint32_t* queue,
   DescRegs dn = load_desc(jn->desc, li, vn);
   while (x.valid) {
     lds_barrier();  // every thread has read s_next; LDS is clear
-    if (threadIdx.x == 0) s_next[0] = atomicAdd(queue, 1u);
+    if (threadIdx.x == 0) s_next[0] = pop.next();
     const GridJob<R>& j = *job;
     GridAcc<R>* s_re = s_lds;
     GridAcc<R>* s_im = s_lds + j.g.T * j.pitch;
@@ -510,7 +541,7 @@ __global__ __launch_bounds__(kGridThreads) void k_grid_tiles(GridJob<R> j) {
   GridAcc<R>* s_lds = reinterpret_cast<GridAcc<R>*>(smem);
   const uint32_t total = item_total(j.counters), nextra = j.counters[2];
   clear_lds(s_lds, 2u * (uint32_t)(j.g.T * j.pitch));
-  item_loop<R, K, KT>(s_lds, &j.counters[3], s_next, &j,
+  item_loop<R, K, KT>(s_lds, &j.counters[3], total, s_next, &j,
                   [&](uint32_t n, const GridJob<R>*&, uint32_t& li) {
                     li = desc_index(j.g, nextra, n);
                     return n < total;
@@ -541,7 +572,7 @@ __global__ __launch_bounds__(kGridThreads) void k_grid_batch(
   }
   clear_lds(s_lds, lds_words);
   lds_barrier();
-  item_loop<R, K, KT>(s_lds, queue, s_next, jobs,
+  item_loop<R, K, KT>(s_lds, queue, s_base[njobs], s_next, jobs,
                   [&](uint32_t n, const GridJob<R>*& jp, uint32_t& li) {
                     int p = 0;
                     const bool live = n < s_base[njobs];
