@@ -95,7 +95,8 @@ typedef int32_t ws_status;
  *   tile     gridding tile edge in cells (power of two, 16..64, > K - 1);
  *            0 = automatic
  *   chunk    most visibilities one gridding work item accumulates before a
- *            split tile is merged; 0 = automatic (4096)
+ *            split tile is merged; 0 = automatic (the least power of two c
+ *            from 512 to 4096 with c^2 >= max_vis)
  *   kernel   WS_KERNEL_GAUSS or WS_KERNEL_ES (sigma applies to the
  *            Gaussian only)
  *   beta     ES kernel shape; <= 0 selects 2.3 K; at most 200

@@ -971,19 +971,39 @@ struct Screen {
   }
 };
 
-// The phasor of plane 0 and the step between planes of pixel (p, q), as
-// Screen forms them.
+// The step between planes of pixel (p, q), as Screen forms it, and the phase
+// its rounding to FP32 adds per plane.
 template <typename R>
-__device__ __forceinline__ cplx<R> screen_at(const Geo& g, int p, int q,
-                                             bool odd) {
-  const cplx<double> a =
-      turns_phasor(fma(g.w0, n_minus_one(g, p, q), odd ? 0.5 : 0.0));
-  return {(R)a.re, (R)a.im};
+__device__ __forceinline__ cplx<R> screen_step(const Geo& g, double nm1,
+                                               R* drift) {
+  const cplx<double> b = turns_phasor(g.dw * nm1);
+  const cplx<R> s = {(R)b.re, (R)b.im};
+  *drift = (R)((double)s.im * b.re - (double)s.re * b.im);
+  return s;
 }
+
+// The phasor of plane 0; `odd` as for Screen.
+__device__ __forceinline__ cplx<double> first_phase(const Geo& g, double nm1,
+                                                    bool odd) {
+  return turns_phasor(fma(g.w0, nm1, odd ? 0.5 : 0.0));
+}
+
+// The phasor ph of the first of `planes` planes, for steps rounded to FP32.
+// Such a step is off by a factor 1 + e, plane k then by (1 + e)^k; the phasor
+// takes (1 + e)^-c, c = (planes - 1) / 2, with it (to first order, e ~ 3e-8),
+// so the error is that of half as many planes, either side of the middle one:
+// a 4096^2 x 32 image 4.8e-7 -> 4.0e-7 off its 64-bit values.
 template <typename R>
-__device__ __forceinline__ cplx<R> screen_step(const Geo& g, int p, int q) {
-  const cplx<double> b = turns_phasor(g.dw * n_minus_one(g, p, q));
-  return {(R)b.re, (R)b.im};
+__device__ __forceinline__ cplx<R> centred(cplx<double> ph, int planes,
+                                           cplx<R> step, R drift) {
+  if constexpr (sizeof(R) == 4) {
+    const double c = 0.5 * (double)(planes - 1);
+    const double re = (double)step.re, im = (double)step.im;
+    const double er = 1.0 - 0.5 * c * fma(re, re, fma(im, im, -1.0));
+    const double ei = -c * (double)drift;
+    ph = {ph.re * er - ph.im * ei, ph.re * ei + ph.im * er};
+  }
+  return {(R)ph.re, (R)ph.im};
 }
 
 // The plane sum sum_k F_k ph_0 step^k by Horner's rule, planes taken last
@@ -1107,23 +1127,36 @@ __global__ __launch_bounds__(row_nt(sizeof(R), LOGN) * G, row_waves(sizeof(R), L
   __shared__ cplx<R> lds_all[G][lds_line<N>(1)];
   __shared__ cplx<R> s_tab[RS::TAB];
   __shared__ cplx<R> s_step[G > 1 ? N : 1];
+  // FP32: the phasors of plane 0, where that leaves as many workgroups per CU
+  // as the registers do (16 wavefronts; not 1024 and 2048 points with G = 1:
+  // seven of eight and three of four, 2% of a 2048^2 image).
+  constexpr bool SEEDS =
+      sizeof(R) == 4 &&
+      (LOGN == 13 || (sizeof(lds_all) + sizeof(s_tab) + sizeof(s_step) +
+                      N * sizeof(cplx<R>)) * (1024 / (NT * G)) <= 160 * 1024);
+  __shared__ cplx<R> s_seed[SEEDS ? N : 1];
   const int q = blockIdx.x;
   const int gi = G == 1 ? 0 : (int)uniform_u32(threadIdx.x / NT);
   const int tid = G == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT;
   cplx<R>* lds = lds_all[gi];
   const auto twl = row_twiddles<R, LOGN>(s_tab, tw, (R)1);
   __syncthreads();
-  // The output centring (-1)^p is half a turn in the screen phase (p has the
-  // parity of the thread index: NT and NB are even).
-  static_assert(NT % 2 == 0 && NB % 2 == 0, "output parity per thread");
-  const bool odd = (tid & 1) != 0;
+  // The output centring (-1)^p is half a turn in the screen phase.
   const int per = (g.nw + G - 1) / G;
   const int k0 = gi * per, k1 = min(k0 + per, g.nw);
   cplx<R> acc[IT][RAD], step[IT][RAD];
-  if constexpr (G > 1) {
-    // Steps of the row's pixels once per workgroup.
-    for (int p = threadIdx.x; p < N; p += NT * G)
-      s_step[p] = screen_step<R>(g, p, q);
+  // Steps (and FP32 seeds) of the row's pixels, once per workgroup and in a
+  // rolled loop: unrolled over a thread's pixels the FP64 functions spill.
+  cplx<R>* steps = G > 1 ? s_step : lds;
+  if constexpr (G > 1 || SEEDS) {
+    for (int p = threadIdx.x; p < N; p += NT * G) {
+      const double nm1 = n_minus_one(g, p, q);
+      R drift;
+      steps[p] = screen_step<R>(g, nm1, &drift);
+      if constexpr (SEEDS)
+        s_seed[p] = centred<R>(first_phase(g, nm1, (p & 1) != 0), g.nw,
+                               steps[p], drift);
+    }
     __syncthreads();
   }
 #pragma unroll
@@ -1133,9 +1166,21 @@ __global__ __launch_bounds__(row_nt(sizeof(R), LOGN) * G, row_waves(sizeof(R), L
       const int j = tid + it * NT, p = j + r * NB;
       acc[it][r] = {(R)0, (R)0};
       step[it][r] = {(R)1, (R)0};
-      if (NB % NT == 0 || j < NB)
-        step[it][r] = G > 1 ? s_step[G > 1 ? p : 0] : screen_step<R>(g, p, q);
+      if (NB % NT == 0 || j < NB) {
+        if constexpr (G > 1 || SEEDS) {
+          step[it][r] = steps[p];
+        } else {
+          R drift;
+          step[it][r] = screen_step<R>(g, n_minus_one(g, p, q), &drift);
+        }
+      }
     }
+  if constexpr (G == 1 && SEEDS) __syncthreads();  // lds is the line again
+  auto seed = [&](int p) -> cplx<R> {
+    if constexpr (SEEDS) return s_seed[p];
+    const cplx<double> a = first_phase(g, n_minus_one(g, p, q), (p & 1) != 0);
+    return {(R)a.re, (R)a.im};
+  };
   using F0 = Stage<R, LOGN, 1, NT, 0, WIDE>;
   constexpr int IT0 = F0::IT, RAD0 = F0::RAD, NB0 = F0::NB;
   // Column-strip marks (64-column strips, T = 64) as bits: samples of strips
@@ -1214,8 +1259,7 @@ __global__ __launch_bounds__(row_nt(sizeof(R), LOGN) * G, row_waves(sizeof(R), L
         if (NB % NT == 0 || j < NB)
           out[p] = cadd(old[it][r],
                         corrected(g, p, q,
-                                  cmul(screen_at<R>(g, p, q, odd),
-                                       acc[it][r])));
+                                  cmul(seed(p), acc[it][r])));
       }
   } else {
     // Group u's part belongs at step^(u per): Horner's rule once more, over
@@ -1239,7 +1283,7 @@ __global__ __launch_bounds__(row_nt(sizeof(R), LOGN) * G, row_waves(sizeof(R), L
         sum = horner_step(sum, sp, lds_all[u][p]);
       out[p] = cadd(out[p],
                     corrected(g, p, q,
-                              cmul(screen_at<R>(g, p, q, (p & 1) != 0), sum)));
+                              cmul(seed(p), sum)));
     }
   }
 }
@@ -1282,10 +1326,12 @@ __global__ __launch_bounds__(row_nt(sizeof(R), LOGN), row_waves(sizeof(R), LOGN)
           v = reinterpret_cast<const cplx<R>*>(img)[(size_t)q * N + p];
         }
         // The phasor of plane k0, its phase formed in FP64.
-        const cplx<double> ph = turns_phasor(
-            fma((double)k0, g.dw, g.w0) * n_minus_one(g, p, q));
-        const cplx<R> a = {(R)ph.re, (R)ph.im};
-        const cplx<R> b = screen_step<R>(g, p, q);
+        const double nm1 = n_minus_one(g, p, q);
+        const cplx<double> ph =
+            turns_phasor(fma((double)k0, g.dw, g.w0) * nm1);
+        R drift;
+        const cplx<R> b = screen_step<R>(g, nm1, &drift);
+        const cplx<R> a = centred<R>(ph, k1 - k0, b, drift);
         x[it][r] = cmul(corrected(g, p, q, v), cplx<R>{a.re, -a.im});
         step[it][r] = {b.re, -b.im};
       }
