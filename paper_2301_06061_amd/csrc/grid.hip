@@ -462,9 +462,9 @@ __device__ __forceinline__ void clear_lds(A* s, uint32_t words) {
 // Queue of the persistent gridders, kept by thread 0 of each workgroup.  All
 // workgroups pop one counter, and atomics on one address run one after the
 // other, 11.5 ns each on this part: popping 91 000 items one by one bounds a
-// launch from below at 1.05 ms.  A pop therefore takes kPopItems items, one from each
-// of as many equal stretches of the queue (its front holds the longest
-// items); the last kPopTail items per workgroup go one by one, for balance.
+// launch from below at 1.05 ms.  A pop therefore takes kPopItems items, one
+// from each of as many equal stretches of the queue (its front holds the
+// longest items); the last kPopTail items per workgroup go one by one, for balance.
 // Those 91 000 items (4096^2 x 32 planes, uniform) 1.36 -> 1.33 ms; 8192^2 x
 // 32, K = 9, 3.01 -> 2.96; 2048^2 x 16 0.246 -> 0.228; 1024^2 x 16 unchanged
 // (0.134).  8 and 16 items a pop leave the ends of smaller launches unbalanced.
