@@ -950,13 +950,11 @@ ws_status batch_image_impl(ws_batch* b, const int64_t* m,
   WS_TRY(launch(p0, "zero_counts", [&] { launch_zero_u32(queue, 1, b->stream); }));
   // As in ws_grid_image, plan by plan: where the imaging reads by tile
   // counts and strip marks, tiles without records are never written; the
-  // other plans' idle tiles get their zeros (the batched zeroing kernel
-  // skips the jobs that need none).
-  bool all_lazy = true;
-  for (int i = 0; i < b->n; ++i) all_lazy = all_lazy && lazy_ok(b->plans[i]);
-  if (!all_lazy) {
-    uint64_t tiles = 0;
-    for (int i = 0; i < b->n; ++i) tiles += (uint64_t)b->plans[i]->g.ntiles;
+  // other plans' idle tiles get their zeros.
+  uint64_t tiles = 0;
+  for (int i = 0; i < b->n; ++i)
+    if (!lazy_ok(b->plans[i])) tiles += (uint64_t)b->plans[i]->g.ntiles;
+  if (tiles != 0) {
     WS_TRY(launch(p0, "zero_idle", [&] {
       launch_zero_idle_batch<R>(reinterpret_cast<const GridJob<R>*>(b->work),
                                 b->n, tiles, b->stream);

@@ -607,17 +607,21 @@ __global__ __launch_bounds__(256) void k_zero_idle(
 }
 
 // Batched form: block b is idle entry b - base(p) of job p, where base(p)
-// sums the tile counts of the jobs before p.
+// sums the tile counts of the jobs before p whose idle tiles need zeros; the
+// others have no blocks.  What bounds it beside its stores is the dispatch of
+// blocks that find nothing to do: with blocks for every plan's tiles, four
+// 1024^2 plans of edge-32 tiles cost a batch of 64 plans 11 of its 83 ms.
 template <typename R>
 __global__ __launch_bounds__(256) void k_zero_idle_batch(
     const GridJob<R>* __restrict__ jobs, int njobs) {
   uint32_t b = blockIdx.x;
   int p = 0;
-  while (p < njobs && b >= (uint32_t)jobs[p].g.ntiles) {
-    b -= (uint32_t)jobs[p].g.ntiles;
-    ++p;
+  for (; p < njobs; ++p) {
+    const uint32_t n = jobs[p].zero_idle ? (uint32_t)jobs[p].g.ntiles : 0u;
+    if (b < n) break;
+    b -= n;
   }
-  if (p >= njobs || !jobs[p].zero_idle || b >= jobs[p].counters[5]) return;
+  if (p >= njobs || b >= jobs[p].counters[5]) return;
   zero_idle_tile(jobs[p].g, jobs[p].idle, b, jobs[p].planes);
 }
 
