@@ -30,6 +30,14 @@ __device__ __forceinline__ uint32_t uniform_u32(uint32_t x) {
   return (uint32_t)__builtin_amdgcn_readfirstlane((int)x);
 }
 
+// A pointer that is the same in all lanes, as a scalar.
+template <typename T>
+__device__ __forceinline__ const T* uniform_ptr(const T* p) {
+  const uint64_t a = reinterpret_cast<uint64_t>(p);
+  const uint64_t hi = uniform_u32((uint32_t)(a >> 32));
+  return reinterpret_cast<const T*>(hi << 32 | uniform_u32((uint32_t)a));
+}
+
 template <typename R>
 __device__ __forceinline__ cplx<R> rot_i(cplx<R> a, R s) {
   // a * (s i)
@@ -136,8 +144,9 @@ struct Twiddles {
   // w[i] = W^(i k N / (NS RAD)), i = 1, 2, 4, 8 < RAD, of stage P: lookups
   // of i = 1 and, for radix 16, i = 4; the others as squares (a few units in
   // the last place).
+  static constexpr bool kAll = false;
   template <int LOGN, bool WIDE, int P, int RAD, int NS>
-  __device__ __forceinline__ void stage(int k, R s, cplx<R>* w) const {
+  __device__ __forceinline__ void stage(int k, int, R s, cplx<R>* w) const {
     constexpr int step = (1 << LOGN) / (NS * RAD);
     w[1] = (*this)(k * step, s);
     if constexpr (RAD > 2) w[2] = cmul(w[1], w[1]);
@@ -228,9 +237,10 @@ constexpr int stage_tw_total(int logn, bool wide) {
 // filled; the other powers are one or two products of these.
 template <typename R>
 struct TableTwiddles {
+  static constexpr bool kAll = false;
   const cplx<R>* tab;
   template <int LOGN, bool WIDE, int P, int RAD, int NS>
-  __device__ __forceinline__ void stage(int k, R, cplx<R>* w) const {
+  __device__ __forceinline__ void stage(int k, int, R, cplx<R>* w) const {
     constexpr int OFF = stage_tw_off(LOGN, WIDE, P);
     w[1] = tab[OFF + k];
     if constexpr (RAD > 2) w[2] = tab[OFF + NS + k];
@@ -240,21 +250,15 @@ struct TableTwiddles {
 };
 
 // Fills the stage table of a length-2^LOGN transform from the global table
-// tw of a length-(stride 2^LOGN) one, conjugated for s = -1.  With
-// `centred_in`, the last stage's entries also carry (-1)^i: a (-1)^e input
-// centring gives every butterfly of the earlier stages one common sign,
-// which the Stockham order carries to input r of the last stage as (-1)^r,
-// so the input needs no sign flips of its own.
+// tw of a length-(stride 2^LOGN) one, conjugated for s = -1.
 template <typename R, int LOGN, bool WIDE>
 __device__ __forceinline__ void fill_stage_twiddles(cplx<R>* tab,
                                                     const cplx<R>* tw, R s,
-                                                    bool centred_in,
-                                                    int stride = 1) {
+                                                    int stride) {
   constexpr int N = 1 << LOGN;
   constexpr int NPASS = stage_npass(LOGN, WIDE);
   for (int i = threadIdx.x; i < stage_tw_total(LOGN, WIDE); i += blockDim.x) {
     int idx = 0;
-    bool neg = false;
 #pragma unroll
     for (int P = 1; P < NPASS; ++P) {
       const int off = stage_tw_off(LOGN, WIDE, P);
@@ -263,22 +267,122 @@ __device__ __forceinline__ void fill_stage_twiddles(cplx<R>* tab,
       if (i >= off && i < off + (bits << lns)) {
         const int l = (i - off) >> lns, k = (i - off) & ((1 << lns) - 1);
         idx = ((k << l) << (LOGN - lns - bits)) & (N - 1);
-        neg = centred_in && P == NPASS - 1 && l == 0;
       }
     }
     const cplx<R> w = tw[(size_t)idx * stride];
-    tab[i] = neg ? cplx<R>{-w.re, -s * w.im} : cplx<R>{w.re, s * w.im};
+    tab[i] = {w.re, s * w.im};
   }
 }
 
-// Inputs r = 1 .. RAD-1 of a butterfly times w[1]^r, from w[1], w[2], w[4],
-// w[8].
-template <typename R, int RAD>
+// Row twiddles: every factor W^(r k N / (NS RAD)), r = 1 .. RAD-1, as the
+// plan's table has it, rounded once (factors formed as products of others
+// carry one or two roundings more: 12-18% on the error of a row transform).
+// The stages in the middle read theirs from LDS, FP32 factors in pairs (r =
+// 1 and 2, 3 and 4, ...: one 16-byte read each).  The last stage's are most
+// of a full table (28 of 32 KB at 4096 FP32 points), and a thread meets the
+// same ones on every plane: they stay in its registers, but for the first LF
+// where LDS has room and registers are short.  Row pass of 32 planes of
+// 4096^2 (FP32 / FP64) and 16 of 2048^2 (FP32), us: factors 1, 2, 4 and
+// products of them 953 / 1970 / 124; these 947 / 1947 / 120; with LF = 0 at
+// 4096 1105 / 2030 (spills); LF = 3 at 2048, which leaves no room for the
+// seeds in LDS, 128.
+template <typename R, int LOGN, int NT>
+struct RowTwiddles {
+  static constexpr bool kAll = true;
+  static constexpr int N = 1 << LOGN;
+  static constexpr int LAST = stage_npass(LOGN, false) - 1;
+  static constexpr int RAD = 1 << stage_bits(LOGN, false, LAST);
+  static constexpr int NS = N / RAD;
+  static constexpr int IT = (NS + NT - 1) / NT;
+  static constexpr int LF =
+      LOGN == 12 ? 2 : (sizeof(R) == 4 && LOGN == 10 ? RAD - 1 : 0);
+  static constexpr bool PAIRS = sizeof(R) == 4;
+  // Factors of stage P in LDS, and the first entry of the stage's.
+  static constexpr int factors(int P) {
+    return P == LAST ? LF : (1 << stage_bits(LOGN, false, P)) - 1;
+  }
+  static constexpr int off(int P) {
+    int o = 0;
+    for (int q = 1; q < P; ++q)
+      o += factors(q) << stage_log_ns(LOGN, false, q);
+    return o;
+  }
+  static constexpr int kTab = off(LAST) + LF * NS;
+  const cplx<R>* tab;  // 16-byte aligned
+  cplx<R> last[IT][RAD];
+
+  // Fills s_tab (kTab entries) and this thread's last stage from the plan's
+  // table, conjugated for s = -1.  The last stage's also carry the input
+  // centring: a (-1)^e factor of the input gives every butterfly of the
+  // earlier stages one common sign, which the Stockham order carries to input
+  // r of the last stage as (-1)^r.
+  __device__ __forceinline__ RowTwiddles(cplx<R>* s_tab, const cplx<R>* tw,
+                                         R s, int tid)
+      : tab(s_tab) {
+    auto entry = [&](int idx, bool neg) -> cplx<R> {
+      const cplx<R> w = tw[idx];
+      return neg ? cplx<R>{-w.re, -s * w.im} : cplx<R>{w.re, s * w.im};
+    };
+    for (int i = threadIdx.x; i < kTab; i += blockDim.x) {
+      int idx = 0;
+      bool neg = false;
+#pragma unroll
+      for (int P = 1; P <= LAST; ++P) {
+        const int lns = stage_log_ns(LOGN, false, P);
+        const int bits = stage_bits(LOGN, false, P);
+        const int j = i - off(P), nf = factors(P);
+        if (j < 0 || j >= nf << lns) continue;
+        int r = (j >> lns) + 1, k = j & ((1 << lns) - 1);
+        if (PAIRS && ((r - 1) | 1) < nf) {
+          const int h = j & ((2 << lns) - 1);
+          r = (j >> (lns + 1)) * 2 + (h & 1) + 1;
+          k = h >> 1;
+        }
+        idx = (r * k) << (LOGN - lns - bits);
+        neg = P == LAST && (r & 1);
+      }
+      s_tab[i] = entry(idx, neg);
+    }
+#pragma unroll
+    for (int it = 0; it < IT; ++it) {
+      const int k = (tid + it * NT) & (NS - 1);
+#pragma unroll
+      for (int r = 1 + LF; r < RAD; ++r) last[it][r] = entry(r * k, r & 1);
+    }
+  }
+  template <int, bool, int P, int SRAD, int SNS>
+  __device__ __forceinline__ void stage(int k, int it, R, cplx<R>* w) const {
+    constexpr int NF = factors(P);
+    const cplx<R>* t = tab + off(P);
+#pragma unroll
+    for (int r = 1; r < SRAD; ++r) {
+      if (r > NF) {
+        w[r] = last[it][r];
+      } else if (PAIRS && ((r - 1) | 1) < NF) {
+        if (r & 1) {
+          struct alignas(2 * sizeof(cplx<R>)) Pair { cplx<R> a, b; };
+          const Pair p =
+              reinterpret_cast<const Pair*>(t + (r - 1) * SNS)[k];
+          w[r] = p.a;
+          w[r + 1] = p.b;
+        }
+      } else {
+        w[r] = t[(r - 1) * SNS + k];
+      }
+    }
+  }
+};
+
+// Inputs r = 1 .. RAD-1 of a butterfly times w[r], given whole (ALL) or as
+// w[1], w[2], w[4], w[8].
+template <typename R, int RAD, bool ALL>
 __device__ __forceinline__ void apply_twiddles(cplx<R>* v, cplx<R>* w) {
+  if constexpr (!ALL) {
 #pragma unroll
-  for (int i = 1; i < RAD; i *= 2) {
+    for (int i = 1; i < RAD; i *= 2) {
 #pragma unroll
-    for (int r = i + 1; r < 2 * i; ++r) w[r] = cmul(w[r - i], w[i]);
+      for (int r = i + 1; r < 2 * i; ++r) w[r] = cmul(w[r - i], w[i]);
+    }
   }
 #pragma unroll
   for (int r = 1; r < RAD; ++r) v[r] = cmul(v[r], w[r]);
@@ -327,8 +431,8 @@ struct Stage {
         if constexpr (NS > 1) {
           // Twiddles W^(r k N / (NS RAD)), r = 1 .. RAD-1.
           cplx<R> w[RAD];
-          tw.template stage<LOGN, WIDE, P, RAD, NS>(k, s, w);
-          apply_twiddles<R, RAD>(v[it], w);
+          tw.template stage<LOGN, WIDE, P, RAD, NS>(k, it, s, w);
+          apply_twiddles<R, RAD, TW::kAll>(v[it], w);
         }
         dft<R, RAD>(v[it], s);
         if constexpr (LAST) {
@@ -795,7 +899,7 @@ __global__ __launch_bounds__(NT) void k_fft_cols_split(
         if (i < kTwLo) f_lo[i] = tw[i];
         else f_hi[i - kTwLo] = tw[(i - kTwLo) * kTwLo];
       }
-      fill_stage_twiddles<R, LOGH, WIDE>(s_tab, tw, s, false, 2);
+      fill_stage_twiddles<R, LOGH, WIDE>(s_tab, tw, s, 2);
       __syncthreads();
       return TableTwiddles<R>{s_tab};
     } else {
@@ -1078,21 +1182,24 @@ struct RowShape {
   static constexpr int GMAX = NT >= 256 ? 1 : 512 / NT;
   static constexpr bool TABLE = LOGN <= 12;
   static constexpr int TAB =
-      TABLE ? stage_tw_total(LOGN, WIDE) : kTwLo + (N + kTwLo - 1) / kTwLo;
+      TABLE ? (RowTwiddles<R, LOGN, NT>::kTab > 0
+                   ? RowTwiddles<R, LOGN, NT>::kTab : 1)
+            : kTwLo + (N + kTwLo - 1) / kTwLo;
   static constexpr bool FITS = LOGN <= 13;
   static constexpr bool SUMS = FITS && NT <= 512;
 };
 
-// Twiddles of a fused row kernel in s_tab (RowShape::TAB entries).  The
-// input centring is folded into the stage table; lookup tables leave it to
-// the caller (odd elements negated as they are loaded).
+// Twiddles of a fused row kernel, with s_tab (RowShape::TAB entries) in LDS.
+// RowTwiddles hold the input centring; lookup tables leave it to the caller
+// (odd elements negated as they are loaded).
 template <typename R, int LOGN>
 __device__ __forceinline__ auto row_twiddles(cplx<R>* s_tab,
-                                             const cplx<R>* tw, R s) {
+                                             const cplx<R>* tw, R s,
+                                             int tid) {
   using RS = RowShape<R, LOGN>;
   if constexpr (RS::TABLE) {
-    fill_stage_twiddles<R, LOGN, RS::WIDE>(s_tab, tw, s, true);
-    return TableTwiddles<R>{s_tab};
+    static_assert(!RS::WIDE, "RowTwiddles are radix 8");
+    return RowTwiddles<R, LOGN, RS::NT>(s_tab, tw, s, tid);
   } else {
     return load_twiddles(s_tab, s_tab + kTwLo, tw, RS::N);
   }
@@ -1109,9 +1216,9 @@ __device__ __forceinline__ auto row_twiddles(cplx<R>* s_tab,
 // Bound by LDS and vector issue together (a 4096-point FP32 line and plane:
 // ~2200 cycles of LDS exchanges, ~2200 of vector instructions per CU).  The
 // row of the next plane is in flight while one is transformed, the strip
-// marks are bits of a wavefront mask read one plane earlier, and stage twiddles
-// are two-thirds products of table entries (half the LDS reads of a full
-// table).  4096 x 4096 x 32 planes: FP32 1.06 -> 0.96 ms, FP64 2.42 -> 1.96.
+// marks are bits of a wavefront mask read one plane earlier, and the largest
+// stage's twiddles are not read again for each plane (RowTwiddles).  4096 x
+// 4096 x 32 planes: FP32 1.07 -> 0.95 ms, FP64 2.42 -> 1.95.
 // 8192 points fused: 32 planes of 8192^2 FP32 10.3 (rows, then screen) -> 5.2.
 template <typename R, int LOGN, int G>
 __global__ __launch_bounds__(row_nt(sizeof(R), LOGN) * G, row_waves(sizeof(R), LOGN))
@@ -1125,11 +1232,11 @@ __global__ __launch_bounds__(row_nt(sizeof(R), LOGN) * G, row_waves(sizeof(R), L
   using L = Stage<R, LOGN, 1, NT, stage_npass(LOGN, WIDE) - 1, WIDE>;
   constexpr int IT = L::IT, RAD = L::RAD, NB = L::NB;
   __shared__ cplx<R> lds_all[G][lds_line<N>(1)];
-  __shared__ cplx<R> s_tab[RS::TAB];
+  __shared__ __align__(16) cplx<R> s_tab[RS::TAB];
   __shared__ cplx<R> s_step[G > 1 ? N : 1];
   // FP32: the phasors of plane 0, where that leaves as many workgroups per CU
-  // as the registers do (16 wavefronts; not 1024 and 2048 points with G = 1:
-  // seven of eight and three of four, 2% of a 2048^2 image).
+  // as the registers do (16 wavefronts; not 1024 points with G = 1: seven of
+  // eight).
   constexpr bool SEEDS =
       sizeof(R) == 4 &&
       (LOGN == 13 || (sizeof(lds_all) + sizeof(s_tab) + sizeof(s_step) +
@@ -1139,7 +1246,7 @@ __global__ __launch_bounds__(row_nt(sizeof(R), LOGN) * G, row_waves(sizeof(R), L
   const int gi = G == 1 ? 0 : (int)uniform_u32(threadIdx.x / NT);
   const int tid = G == 1 ? (int)threadIdx.x : (int)threadIdx.x % NT;
   cplx<R>* lds = lds_all[gi];
-  const auto twl = row_twiddles<R, LOGN>(s_tab, tw, (R)1);
+  const auto twl = row_twiddles<R, LOGN>(s_tab, tw, (R)1, tid);
   __syncthreads();
   // The output centring (-1)^p is half a turn in the screen phase.
   const int per = (g.nw + G - 1) / G;
@@ -1216,8 +1323,15 @@ __global__ __launch_bounds__(row_nt(sizeof(R), LOGN) * G, row_waves(sizeof(R), L
     if (NB0 % NT == 0 || j < NB0) {
       const int e = j + r * NB0;
       const int sb = kUniform ? (int)uniform_u32(e >> 6) : e >> 6;
-      if ((mask[MW > 1 ? sb >> 6 : 0] >> (sb & 63)) & 1ull)
-        buf[it][r] = planes[(size_t)(k0 + n) * g.nv * N + row + e];
+      if ((mask[MW > 1 ? sb >> 6 : 0] >> (sb & 63)) & 1ull) {
+        const cplx<R>* line = planes + (size_t)(k0 + n) * g.nv * N + row;
+        // FP32: a scalar base and the thread's index, or the addresses of
+        // the thread's samples take registers that the factors need.
+        if constexpr (sizeof(R) == 4)
+          buf[it][r] = uniform_ptr(line + it * NT + r * NB0)[(uint32_t)tid];
+        else
+          buf[it][r] = line[e];
+      }
     }
   };
   load_marks(per - 1);
@@ -1302,9 +1416,10 @@ __global__ __launch_bounds__(row_nt(sizeof(R), LOGN), row_waves(sizeof(R), LOGN)
   using F0 = Stage<R, LOGN, 1, NT, 0, WIDE>;
   constexpr int IT = F0::IT, RAD = F0::RAD, NB = F0::NB;
   __shared__ cplx<R> lds[lds_line<N>(1)];
-  __shared__ cplx<R> s_tab[RS::TAB];
+  __shared__ __align__(16) cplx<R> s_tab[RS::TAB];
   const int q = blockIdx.x;
-  const auto twl = row_twiddles<R, LOGN>(s_tab, tw, (R)-1);
+  const auto twl = row_twiddles<R, LOGN>(s_tab, tw, (R)-1,
+                                          (int)threadIdx.x);
   __syncthreads();
   const int per = (g.nw + gridDim.y - 1) / gridDim.y;
   const int k0 = (int)blockIdx.y * per, k1 = min(k0 + per, g.nw);
