@@ -334,9 +334,16 @@ ws_status ws_clean_minor(ws_plan* plan, void* residual, const void* beam,
  *   params, m, uvw, vis, weight, n_dropped_taps: as for ws_grid_image;
  *   image: device [nv][nu] complex of the plan precision, ADDED to;
  *   hip_stream: the stream to enqueue on (NULL = the null stream).
- * A problem whose stack plus workspace (ws_workspace_bytes with max_vis =
- * m, the stack rounded up to 256 bytes) exceeds WS_NOALLOC_SCRATCH_BYTES is
- * refused with WS_WORKSPACE_TOO_SMALL before any device work.  Every call
+ * A problem whose stack (rounded up to 256 bytes) plus workspace exceeds
+ * WS_NOALLOC_SCRATCH_BYTES is refused with WS_WORKSPACE_TOO_SMALL before any
+ * device work.  The workspace that decides is one with the partition's (or
+ * the hashed sort's) buffers, items of params->chunk records (4096 when
+ * automatic) and partial tiles of split tiles in the plan's precision: some
+ * 85 bytes (FP32) or 135 (FP64) a visibility, and 64 tiles.  It is not what
+ * ws_workspace_bytes reports: a plan sorts small problems in one level, and
+ * makes smaller items with more and FP64 partial tiles.  This call does the
+ * same as far as the scratch allows and otherwise makes its items larger (up
+ * to 4096 records), then keeps fewer partial tiles.  Every call
  * on one GPU shares that GPU's scratch: calls that overlap in time on one
  * GPU (two streams, two threads) race and give wrong images; serialise
  * them.  The scratch keeps the last call's contents; each call clears what

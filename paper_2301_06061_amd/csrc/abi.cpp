@@ -181,14 +181,30 @@ uint32_t auto_chunk(int64_t max_vis) {
 }
 
 // Scratch slots for the partial tiles of split tiles, and the bytes of one.
+// A tile that finds too few left becomes one work item, however many records
+// it has, so the slots are sized for twice the visibilities (a dense core
+// on a corner of four tiles reads each up to two times on average).
 constexpr int64_t kMaxSlots = 4096;
+int64_t wanted_slots(int64_t max_vis, uint32_t chunk) {
+  return std::min(2 * max_vis / chunk + 64, kMaxSlots);
+}
 size_t partial_bytes(const Layout& L) {
   return (size_t)L.T * L.T * 2 *
          (L.elem == 16 ? sizeof(GridAcc<double>) : sizeof(GridAcc<float>));
 }
 
+// How make_layout sizes a plan.
+struct Sizing {
+  uint32_t chunk_at_least = 0;     // automatic chunks (raised up to 4096)
+  int64_t max_slots = kMaxSlots;   // partial-tile slots
+  // The size ws_grid_image_noalloc is admitted by: the two-level sort or the
+  // hashed one, items of 4096 records (automatic), partial tiles in the
+  // plan's precision, and eight bytes for every further item.
+  bool admission = false;
+};
+
 ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
-                      int64_t max_slots = kMaxSlots) {
+                      const Sizing& z = Sizing()) {
   ws_status st = check_params(p);
   if (st != WS_OK) return st;
   if (max_vis < 1 || max_vis > kMaxVis)
@@ -199,7 +215,9 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
   if (L->T <= p->support - 1)
     return fail(WS_UNSUPPORTED_SIZE, "grid %d too small for support %d", nmin,
                 p->support);
-  L->chunk = p->chunk != 0 ? (uint32_t)p->chunk : auto_chunk(max_vis);
+  L->chunk = p->chunk != 0  ? (uint32_t)p->chunk
+             : z.admission ? 4096u
+                           : std::max(auto_chunk(max_vis), z.chunk_at_least);
   L->elem = p->precision == WS_FP64 ? 16 : 8;
   const int64_t tu = p->nu / L->T, tv = p->nv / L->T;
   L->ntiles = tu * tv * p->nw;
@@ -226,10 +244,10 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
                      ? WS_BINNING_HASHED : WS_BINNING_PARTITION;
     L->part_buckets = (uint32_t)buckets;
     L->part_span = (uint32_t)span;
-    L->direct = p->binning == WS_BINNING_AUTO && direct_fits(max_vis, L->nkeys);
+    L->direct = !z.admission && p->binning == WS_BINNING_AUTO &&
+                direct_fits(max_vis, L->nkeys);
   }
-  int64_t slots = 2 * max_vis / L->chunk + 64;
-  if (slots > max_slots) slots = max_slots;
+  const int64_t slots = std::min(wanted_slots(max_vis, L->chunk), z.max_slots);
   L->max_slots = (uint32_t)slots;
   // Further work items beyond one per tile: at most max_slots when
   // gridding (split tiles hold scratch slots), at most max_vis / chunk when
@@ -299,7 +317,9 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
   // the reset wrote records into.
   L->o_strips = take((size_t)p->nw * (p->nu / L->T) * 4);
   // Partial tiles hold the gridder's FP64 sums on both paths.
-  L->o_partials = take(L->max_slots * partial_bytes(*L));
+  L->o_partials = take(z.admission ? (size_t)slots * L->T * L->T * L->elem
+                                   : (size_t)slots * partial_bytes(*L));
+  if (z.admission) take((size_t)L->max_extra * 8);
   // One plane of scratch for the natural-order output of ws_fft_planes
   // when columns use the four-step transform.
   L->o_scratch = take(p->nv > kOnePassCols
@@ -1281,27 +1301,40 @@ ws_status ws_grid_image_noalloc(const ws_params* params, int64_t m,
                                 int64_t* n_dropped_taps, void* hip_stream) {
   // Sizes first (host only): a problem that does not fit the scratch is
   // refused before any device work.
+  const int64_t mv = m > 0 ? m : 1;
   Layout L;
-  WS_TRY(make_layout(params, m > 0 ? m : 1, &L));
+  Sizing z;
+  z.admission = true;
+  WS_TRY(make_layout(params, mv, &L, z));
   const size_t planes_at = 0;
   const size_t work_at = align_up(L.planes_bytes, 256);
-  size_t need = work_at + L.total;
-  if (need > kNoAllocBytes && L.max_slots > 1) {
-    // Partial-tile slots only spread split tiles over more workgroups: near
-    // the limit the problem keeps as many as fit.
-    const size_t over = need - kNoAllocBytes, pb = partial_bytes(L);
-    const size_t drop = (over + 255) / pb + 1;
-    WS_TRY(make_layout(params, m > 0 ? m : 1, &L,
-                       drop < L.max_slots ? (int64_t)(L.max_slots - drop)
-                                          : 1));
-    need = work_at + L.total;
-  }
+  const size_t need = work_at + L.total;
   if (need > kNoAllocBytes)
     return fail(WS_WORKSPACE_TOO_SMALL,
                 "this problem needs %zu bytes of stack and workspace; the "
                 "allocation-free call has a %zu-byte static scratch (use "
                 "ws_grid_init with caller buffers instead)",
                 need, kNoAllocBytes);
+  // Near the limit the partial-tile slots get what is left: first larger
+  // items, which need fewer, then, at 4096 records, as many slots as there is
+  // room for (half of the admission size's at least).  A tile without slots
+  // is one work item: 1e5 visibilities in one tile of 1024^2 x 6 planes take
+  // 1420 us with 181 slots for items of 512 records, 130 us in items of 2048.
+  z.admission = false;
+  WS_TRY(make_layout(params, mv, &L, z));
+  while (work_at + L.total > kNoAllocBytes && params->chunk == 0 &&
+         L.chunk < 4096) {
+    z.chunk_at_least = 2 * L.chunk;
+    WS_TRY(make_layout(params, mv, &L, z));
+  }
+  if (work_at + L.total > kNoAllocBytes) {
+    const size_t drop =
+        (work_at + L.total - kNoAllocBytes + 255) / partial_bytes(L) + 1;
+    z.max_slots = drop < L.max_slots ? (int64_t)(L.max_slots - drop) : 1;
+    WS_TRY(make_layout(params, mv, &L, z));
+  }
+  if (work_at + L.total > kNoAllocBytes)
+    return fail(WS_WORKSPACE_TOO_SMALL, "the static scratch is too small");
   if (image == nullptr) return fail(WS_INVALID_ARG, "image is NULL");
   if (m > 0 && vis == nullptr) return fail(WS_INVALID_ARG, "vis is NULL");
   int dev = 0;
