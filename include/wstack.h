@@ -95,8 +95,13 @@ typedef int32_t ws_status;
  *   tile     gridding tile edge in cells (power of two, 16..64, > K - 1);
  *            0 = automatic
  *   chunk    most visibilities one gridding work item accumulates before a
- *            split tile is merged; 0 = automatic (the least power of two c
- *            from 512 to 4096 with c^2 >= max_vis)
+ *            split tile is merged; 0 = automatic: the least power of two c
+ *            from 512 to 4096 with c^2 >= max_vis whose partial tiles of
+ *            split tiles (2 max_vis / c + 64, at most 4096, 64 KB each for
+ *            tile edge 64) take at most 128 MiB or a sixteenth of the plane
+ *            stack.  In a batch, items are at least as large as all its
+ *            plans' max_vis together give by the first rule: a program that
+ *            knows its batch saves workspace by asking for that chunk
  *   kernel   WS_KERNEL_GAUSS or WS_KERNEL_ES (sigma applies to the
  *            Gaussian only)
  *   beta     ES kernel shape; <= 0 selects 2.3 K; at most 200

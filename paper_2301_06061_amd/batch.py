@@ -19,6 +19,16 @@ from . import _abi
 from .api import WStackPlan, _ptr
 
 
+def batch_chunk(max_vis: Sequence[int]) -> int:
+    """Records per work item that ws_batch_image uses for plans with
+    automatic chunks: the least power of two c from 512 to 4096 whose square
+    reaches the visibilities of all plans together."""
+    c = 512
+    while c < 4096 and c * c < sum(max_vis):
+        c *= 2
+    return c
+
+
 class BatchedImager:
     def __init__(self, workloads: Sequence, uvw: Sequence[torch.Tensor],
                  vis: Sequence[torch.Tensor],
@@ -38,6 +48,7 @@ class BatchedImager:
         self.weight = list(weight) if weight is not None else [None] * n
         self.plans: List[WStackPlan] = []
         self.tuned = []
+        counts = [max(1, int(u.shape[0])) for u in self.uvw]
         with torch.cuda.stream(self.stream):
             for i, wl in enumerate(workloads):
                 tile, chunk = 0, 0
@@ -51,8 +62,11 @@ class BatchedImager:
                 p = WStackPlan(wl.nu, wl.nv, wl.nw, wl.fov_l, wl.fov_m,
                                wl.w_min, wl.w_max, wl.support,
                                getattr(wl, "sigma", 0.0), precision,
-                               max_vis=max(1, int(self.uvw[i].shape[0])),
-                               tile=tile, chunk=chunk, device=self.device,
+                               max_vis=counts[i], tile=tile,
+                               # Workspaces for the batch's items, not for
+                               # the smaller ones of a plan by itself.
+                               chunk=chunk or batch_chunk(counts),
+                               device=self.device,
                                kernel=getattr(wl, "kernel", "gauss"),
                                beta=getattr(wl, "beta", 0.0),
                                correct=bool(getattr(wl, "correct", False)))

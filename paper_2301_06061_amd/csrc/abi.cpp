@@ -192,6 +192,14 @@ size_t partial_bytes(const Layout& L) {
   return (size_t)L.T * L.T * 2 *
          (L.elem == 16 ? sizeof(GridAcc<double>) : sizeof(GridAcc<float>));
 }
+// Automatic items smaller than 4096 records cost slots: up to 4 KB of partial
+// tiles a visibility for edge-64 tiles (at 512 records; 0.5 KB at 4096).
+// They may take 128 MiB or a sixteenth of the plane stack together: 1e6
+// visibilities keep items of 1024 (2017 slots), 4e6 on less than 2 GB of
+// planes take 4096 instead of 2048 (a 512^2 x 4 image 629 us against 633).
+size_t partial_budget(const Layout& L) {
+  return std::max((size_t)128 << 20, L.planes_bytes / 16);
+}
 
 // How make_layout sizes a plan.
 struct Sizing {
@@ -215,10 +223,15 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
   if (L->T <= p->support - 1)
     return fail(WS_UNSUPPORTED_SIZE, "grid %d too small for support %d", nmin,
                 p->support);
+  L->elem = p->precision == WS_FP64 ? 16 : 8;
+  L->planes_bytes = (size_t)p->nw * p->nv * p->nu * L->elem;
   L->chunk = p->chunk != 0  ? (uint32_t)p->chunk
              : z.admission ? 4096u
                            : std::max(auto_chunk(max_vis), z.chunk_at_least);
-  L->elem = p->precision == WS_FP64 ? 16 : 8;
+  while (p->chunk == 0 && L->chunk < 4096 &&
+         wanted_slots(max_vis, L->chunk) * partial_bytes(*L) >
+             partial_budget(*L))
+    L->chunk *= 2;
   const int64_t tu = p->nu / L->T, tv = p->nv / L->T;
   L->ntiles = tu * tv * p->nw;
   L->nkeys = L->ntiles * kRegions;
@@ -254,7 +267,6 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
   // degridding (each record is read by one tile).
   const int64_t ex = max_vis / L->chunk + 2;
   L->max_extra = (uint32_t)(ex > slots ? ex : slots);
-  L->planes_bytes = (size_t)p->nw * p->nv * p->nu * L->elem;
   const size_t A = 256;
   size_t o = 0;
   auto take = [&](size_t bytes) {
