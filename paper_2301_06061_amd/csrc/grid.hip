@@ -715,14 +715,32 @@ __device__ __forceinline__ int stack_row_fast(const Geo& g, int q) {
 // eight XCDs in turn), so that neighbouring tiles share their halo in its L2.
 //
 // Bound by the tiles' loads and their latency: a 64 x 64 FP32 tile with its
-// halo is 39 KB, four workgroups a CU.  Tiles of at most kDegridDirect records
-// do not load it: K lanes take one record each (one kernel row a lane) and
-// read its cells from the stack, about 1 KB a record.  Denser tiles are
+// halo is 39 KB, four workgroups a CU.  Tiles of at most degrid_direct()
+// records do not load it: K lanes take one record each (one kernel row a
+// lane) and read its cells from the stack.  Denser tiles are
 // staged in LDS, aligned rows of T cells two (FP32) a load and the 2 H halo
 // columns apart, with the first records in flight behind them; then one record
 // a lane.  4096^2 x 32 planes, 1e7 visibilities: 1.62 -> 0.65 ms.
 constexpr int kDegridRun = 64;
-constexpr uint32_t kDegridDirect = 32;
+
+// Records up to which a tile is read directly: the counts where reading
+// directly and staging the tile take the same time, on full stacks of tiles
+// with equal counts (1024^2 x 32 planes of 64-cell tiles, x 8 of 32 and 16).
+// Reading takes a round of loads for every 4 * (64 / K) records, staging the
+// tile's own loads and then a record a lane, almost whatever their number.
+// us at 32 records, direct / staged: K = 7 on 64-cell tiles 46 / 60 (FP32), 98
+// / 155 (FP64); K = 15 129 / 99, 300 / 362; on 32-cell tiles 105 / 46, 124 /
+// 88.  16- and 32-cell tiles meet within 3 records of each other; K = 13 lies
+// between its neighbours; more than 64 was not measured.
+constexpr uint32_t degrid_direct(int K, int T, int real_bytes) {
+  constexpr uint8_t at[2][2][8] = {
+      // K = 1, 3, 5, 7, 9, 11, 13, 15
+      {{64, 64, 50, 30, 19, 13, 11, 10},    // FP32, 16 and 32 cells
+       {64, 64, 60, 41, 34, 25, 23, 21}},   // FP32, 64 cells
+      {{64, 64, 48, 42, 28, 21, 19, 17},    // FP64
+       {64, 64, 64, 64, 50, 42, 42, 42}}};
+  return at[real_bytes == 8][T == 64][(K - 1) / 2];
+}
 
 // Sum over the K lanes of a record's group (rows 0 .. K-1), valid on row 0.
 template <typename R, int K>
@@ -740,10 +758,17 @@ __device__ __forceinline__ R row_sum(R v, int row) {
   return v;
 }
 
+// Wavefronts per SIMD to compile for: FP32 and K <= 5 lie at the border of six
+// (82 registers and five cost 16- and 32-cell tiles 10%).
+constexpr int degrid_waves(int K, int real_bytes) {
+  return real_bytes == 4 && K <= 5 ? 6 : 1;
+}
+
 template <typename R, int K, int KT>
-__global__ __launch_bounds__(256) void k_degrid_tiles(
+__global__ __launch_bounds__(256, degrid_waves(K, sizeof(R)))
+    void k_degrid_tiles(
     Geo g, const uint32_t* __restrict__ counters,
-    const uint4* __restrict__ desc, uint32_t extra_blocks,
+    const uint4* __restrict__ desc, uint32_t extra_blocks, uint32_t direct,
     const cplx<R>* __restrict__ planes, const Record<R>* __restrict__ rec,
     cplx<R>* __restrict__ vis_out) {
   constexpr int H = (K - 1) / 2;
@@ -770,7 +795,7 @@ __global__ __launch_bounds__(256) void k_degrid_tiles(
   tile_origin(g, (int)d.x, k, oy, ox);
   const cplx<R>* src = planes + (size_t)k * g.nv * g.nu;
   const int lane = (int)threadIdx.x & 63, wave = wave_index();
-  if (end - start <= kDegridDirect) {
+  if (end - start <= direct) {
     using RL = RowLanes<K>;
     const int slot = lane / K, row = lane - slot * K;
     const bool act = slot < RL::RPW;
@@ -990,8 +1015,9 @@ void degrid_k(const Geo& g, const uint32_t* counters, const uint32_t* desc,
   const uint32_t tiles = ((uint32_t)g.ntiles + per - 1) / per * per;
   hipLaunchKernelGGL((k_degrid_tiles<R, K, KT>), dim3(max_extra + tiles),
                      dim3(256), lds, st, g, counters, (const uint4*)desc,
-                     max_extra, (const cplx<R>*)planes,
-                     (const Record<R>*)records, (cplx<R>*)vis_out);
+                     max_extra, degrid_direct(K, g.T, sizeof(R)),
+                     (const cplx<R>*)planes, (const Record<R>*)records,
+                     (cplx<R>*)vis_out);
 }
 
 }  // namespace
