@@ -386,20 +386,22 @@ __device__ __forceinline__ TileRecords tile_records(const Geo& g, int t,
   return r;
 }
 
-// Cuts tile t into work items and writes everything later passes read about
-// it: its chunk count (0 marks a tile without records, whose stack cells may
-// be left unwritten by a fused grid-and-image call), its entry `at` in the
-// busy or idle list, its column strip's mark, the scratch slots of a split
-// tile, and (gridding) one descriptor per item.  ctr: [0] scratch slots
-// taken, [1] split tiles, [2] extra items; in LDS or in device memory.
-__device__ __forceinline__ void emit_tile(const Geo& g, const TileWork& w,
-                                          int t, const TileRecords& r,
-                                          uint32_t at, uint32_t* ctr) {
-  if (r.work == 0) {
+// Cuts tile t into work items and writes what later passes read about it: its
+// chunk count (0 marks a tile without records, whose stack cells may be left
+// unwritten by a fused grid-and-image call), its entry `at` in the busy or
+// idle list, its column strip's mark and the scratch slots of a split tile.
+// Returns the chunk count, and in e0 the first of its extra items.  ctr: [0]
+// scratch slots taken, [1] split tiles, [2] extra items; in LDS or in device
+// memory.
+__device__ __forceinline__ uint32_t emit_tile(const Geo& g, const TileWork& w,
+                                              int t, uint32_t work,
+                                              uint32_t at, uint32_t* ctr,
+                                              uint32_t& e0) {
+  if (work == 0) {
     w.idle[at] = (uint32_t)t;
     w.tile_slot[t] = 0;
     w.tile_chunks[t] = 0u;
-    return;
+    return 0;
   }
   w.busy[at] = (uint32_t)t;
   if (w.tslot != nullptr) w.tslot[t] = at;  // its slot in the busy-tile store
@@ -410,7 +412,7 @@ __device__ __forceinline__ void emit_tile(const Geo& g, const TileWork& w,
     const int tx = (t - k * per_plane) % g.tiles_u;
     w.strips[k * g.tiles_u + tx] = 1u;
   }
-  uint32_t nch = (r.work + w.chunk - 1) / w.chunk;
+  uint32_t nch = (work + w.chunk - 1) / w.chunk;
   uint32_t slot = 0;
   if (nch > 1 && !w.degrid) {
     const uint32_t s0 = atomicAdd(&ctr[0], nch);
@@ -421,7 +423,6 @@ __device__ __forceinline__ void emit_tile(const Geo& g, const TileWork& w,
       nch = 1;  // scratch exhausted: one item grids the whole tile
     }
   }
-  uint32_t e0 = 0;
   if (nch > 1) {
     e0 = atomicAdd(&ctr[2], nch - 1);
     if (e0 + (nch - 1) > w.max_extra)
@@ -429,42 +430,96 @@ __device__ __forceinline__ void emit_tile(const Geo& g, const TileWork& w,
   }
   w.tile_slot[t] = slot;
   w.tile_chunks[t] = nch;
-  if (w.degrid) {
-    const uint32_t end = r.first[0] + r.work;
-    for (uint32_t c = 0; c < nch; ++c) {
-      const uint32_t b = r.first[0] + c * w.chunk;
-      const size_t n = c == 0 ? (size_t)at : (size_t)g.ntiles + e0 + c - 1;
-      reinterpret_cast<uint4*>(w.desc)[n] = make_uint4(
-          (uint32_t)t, b, nch == 1 ? end : min(end, b + w.chunk), 0u);
-    }
-    return;
-  }
-  // Descriptors (layout: kDescWords in ws_kernels.h).
-  uint32_t d[kDescWords];
+  return nch;
+}
+
+// What the descriptors of one tile hold (see kDescWords in ws_kernels.h).
+struct TileDesc {
+  uint32_t tile, nch, work, at, e0;
+  uint32_t first;                       // degridding: its first record
+  uint32_t ranges[2 * kSegments - 1];   // gridding: words 5 ..
+};
+
+__device__ __forceinline__ TileDesc tile_desc(const TileWork& w, int t,
+                                              const TileRecords& r,
+                                              uint32_t nch, uint32_t at,
+                                              uint32_t e0) {
+  TileDesc d = {};
+  d.tile = (uint32_t)t;
+  d.nch = nch;
+  d.work = r.work;
+  d.at = at;
+  d.e0 = e0;
+  d.first = r.first[0];
+  if (w.degrid || nch == 0) return d;
   uint32_t cum = 0, prev = 0;
 #pragma unroll
   for (int s = 0; s < kSegments; ++s) {
     const uint32_t off = r.first[s] - cum;
     if (s == 0) {
-      d[5] = off;
+      d.ranges[0] = off;
     } else {
-      d[5 + s] = cum;
-      d[5 + kSegments - 1 + s] = off - prev;
+      d.ranges[s] = cum;
+      d.ranges[kSegments - 1 + s] = off - prev;
     }
     prev = off;
     cum += r.len[s];
   }
-  d[0] = (uint32_t)t;
-  d[1] = nch;
-  for (uint32_t c = 0; c < nch; ++c) {
-    d[2] = nch == 1 ? at : c;
-    d[3] = c * w.chunk;
-    d[4] = nch == 1 ? cum : min(cum, (c + 1) * w.chunk);
-    const size_t n = c == 0 ? (size_t)at : (size_t)g.ntiles + e0 + c - 1;
-    uint4* p = reinterpret_cast<uint4*>(w.desc + n * kDescWords);
+  return d;
+}
+
+// Descriptor of chunk c.
+__device__ __forceinline__ void put_desc(const Geo& g, const TileWork& w,
+                                         const TileDesc& d, uint32_t c) {
+  const size_t n = c == 0 ? (size_t)d.at : (size_t)g.ntiles + d.e0 + c - 1;
+  uint4* p = reinterpret_cast<uint4*>(w.desc);
+  if (w.degrid) {
+    const uint32_t b = d.first + c * w.chunk, end = d.first + d.work;
+    p[n] = make_uint4(d.tile, b, d.nch == 1 ? end : min(end, b + w.chunk), 0u);
+    return;
+  }
+  uint32_t o[kDescWords];
+  o[0] = d.tile;
+  o[1] = d.nch;
+  o[2] = d.nch == 1 ? d.at : c;
+  o[3] = c * w.chunk;
+  o[4] = d.nch == 1 ? d.work : min(d.work, (c + 1) * w.chunk);
 #pragma unroll
-    for (int q = 0; q < kDescWords / 4; ++q)
-      p[q] = make_uint4(d[4 * q], d[4 * q + 1], d[4 * q + 2], d[4 * q + 3]);
+  for (int q = 5; q < kDescWords; ++q) o[q] = d.ranges[q - 5];
+  p += n * (kDescWords / 4);
+#pragma unroll
+  for (int q = 0; q < kDescWords / 4; ++q)
+    p[q] = make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
+}
+
+// Descriptors of the items of a wavefront's tiles (one a lane, nch = 0 for
+// none; all 64 lanes call).  A lane writes its own tile's, but those of a tile
+// of more than kOwnDescs chunks are spread over the wavefront: one lane takes
+// 80 ns for each, and the hottest tile may have thousands (1221 chunks of
+// 4096: 101 -> 11 us; 19 532 degridding chunks of 256: 708 -> 27).
+constexpr uint32_t kOwnDescs = 16;
+__device__ __forceinline__ void emit_descs(const Geo& g, const TileWork& w,
+                                           const TileDesc& d) {
+  const bool own = d.nch <= kOwnDescs;
+  for (uint32_t c = 0; own && c < d.nch; ++c) put_desc(g, w, d, c);
+  unsigned long long rest = __ballot(!own);
+  while (rest != 0) {
+    const int l = __ffsll((long long)rest) - 1;
+    rest &= rest - 1;
+    auto of = [&](uint32_t v) {
+      return (uint32_t)__builtin_amdgcn_readlane((int)v, l);
+    };
+    TileDesc o;
+    o.tile = of(d.tile);
+    o.nch = of(d.nch);
+    o.work = of(d.work);
+    o.at = of(d.at);
+    o.e0 = of(d.e0);
+    o.first = of(d.first);
+#pragma unroll
+    for (int q = 0; q < 2 * kSegments - 1; ++q) o.ranges[q] = of(d.ranges[q]);
+    for (uint32_t c = threadIdx.x & 63u; c < o.nch; c += 64u)
+      put_desc(g, w, o, c);
   }
 }
 
@@ -519,7 +574,9 @@ __global__ __launch_bounds__(kTileWorkThreads) void k_tile_work(
   for (int q = 0; q < wave; ++q) at += s_cnt[which][q];
   at += (uint32_t)__popcll((which == 0 ? bmask : imask) &
                            ((1ull << lane) - 1ull));
-  if (live) emit_tile(g, w, t, r, at, counters);
+  uint32_t nch = 0, e0 = 0;
+  if (live) nch = emit_tile(g, w, t, r.work, at, counters, e0);
+  emit_descs(g, w, tile_desc(w, t, r, nch, at, e0));
 }
 
 // ---- two-level partition (no global atomics) ------------------------------
@@ -1122,7 +1179,10 @@ __global__ __launch_bounds__(kPartThreads) void k_direct_tiles(
     const uint32_t ib = wave_append(&s_ctr[4], live && r.work > 0);
     const uint32_t ii = wave_append(&s_ctr[5], live && r.work == 0);
     if (r.work > 0) atomicAdd(&s_reads, (unsigned long long)r.work);
-    if (live) emit_tile(g, w, t, r, r.work > 0 ? ib : ii, s_ctr);
+    const uint32_t at = r.work > 0 ? ib : ii;
+    uint32_t nch = 0, e0 = 0;
+    if (live) nch = emit_tile(g, w, t, r.work, at, s_ctr, e0);
+    emit_descs(g, w, tile_desc(w, t, r, nch, at, e0));
   }
   __syncthreads();
   if (threadIdx.x < 6) w.counters[threadIdx.x] = s_ctr[threadIdx.x];
