@@ -711,8 +711,11 @@ __device__ __forceinline__ int stack_row_fast(const Geo& g, int q) {
 
 // Degridding.  One workgroup per item (descriptor: tile and its record
 // range), the extra chunks of large tiles first; blocks past the item counts
-// exit.  Runs of kDegridRun items go to one XCD (blocks are dealt to the
-// eight XCDs in turn), so that neighbouring tiles share their halo in its L2.
+// exit.  Items are taken in list order, which the device deals to its eight
+// XCDs in turn: keeping runs of 64 neighbours (shared halos) on one XCD gained
+// nothing on large plans (4096^2 x 32 planes 625 us, in turn 618) and left a
+// plan of 128 tiles two XCDs (256^2 x 8, 50 021 visibilities, ES, FP64: 22 us,
+// in turn 16; runs of 8: 16 and 627).
 //
 // Bound by the tiles' loads and their latency: a 64 x 64 FP32 tile with its
 // halo is 39 KB, four workgroups a CU.  Tiles of at most degrid_direct()
@@ -720,8 +723,7 @@ __device__ __forceinline__ int stack_row_fast(const Geo& g, int q) {
 // lane) and read its cells from the stack.  Denser tiles are
 // staged in LDS, aligned rows of T cells two (FP32) a load and the 2 H halo
 // columns apart, with the first records in flight behind them; then one record
-// a lane.  4096^2 x 32 planes, 1e7 visibilities: 1.62 -> 0.65 ms.
-constexpr int kDegridRun = 64;
+// a lane.  4096^2 x 32 planes, 1e7 visibilities: 1.62 -> 0.62 ms.
 
 // Records up to which a tile is read directly: the counts where reading
 // directly and staging the tile take the same time, on full stacks of tiles
@@ -730,8 +732,8 @@ constexpr int kDegridRun = 64;
 // tile's own loads and then a record a lane, almost whatever their number.
 // us at 32 records, direct / staged: K = 7 on 64-cell tiles 46 / 60 (FP32), 98
 // / 155 (FP64); K = 15 129 / 99, 300 / 362; on 32-cell tiles 105 / 46, 124 /
-// 88.  16- and 32-cell tiles meet within 3 records of each other; K = 13 lies
-// between its neighbours; more than 64 was not measured.
+// 88.  16- and 32-cell tiles cross within a fifth of each other and share a
+// count; K = 13 lies between its neighbours; more than 64 was not measured.
 constexpr uint32_t degrid_direct(int K, int T, int real_bytes) {
   constexpr uint8_t at[2][2][8] = {
       // K = 1, 3, 5, 7, 9, 11, 13, 15
@@ -782,11 +784,7 @@ __global__ __launch_bounds__(256, degrid_waves(K, sizeof(R)))
     d = desc[(size_t)g.ntiles + blockIdx.x];
     if (blockIdx.x >= counters[2]) return;
   } else {
-    const uint32_t b = blockIdx.x - extra_blocks;
-    const uint32_t x = b % 8u, n = b / 8u;
-    const uint32_t item =
-        ((n / kDegridRun) * 8u + x) * kDegridRun + n % kDegridRun;
-    if (item >= (uint32_t)g.ntiles) return;
+    const uint32_t item = blockIdx.x - extra_blocks;
     d = desc[item];
     if (item >= counters[4]) return;
   }
@@ -1010,10 +1008,8 @@ void degrid_k(const Geo& g, const uint32_t* counters, const uint32_t* desc,
               void* vis_out, hipStream_t st) {
   const int W = g.T + (K - 1);
   const size_t lds = (size_t)W * W * sizeof(cplx<R>);
-  // Blocks for every tile, whole runs on every XCD.
-  const uint32_t per = 8u * kDegridRun;
-  const uint32_t tiles = ((uint32_t)g.ntiles + per - 1) / per * per;
-  hipLaunchKernelGGL((k_degrid_tiles<R, K, KT>), dim3(max_extra + tiles),
+  hipLaunchKernelGGL((k_degrid_tiles<R, K, KT>),
+                     dim3(max_extra + (uint32_t)g.ntiles),
                      dim3(256), lds, st, g, counters, (const uint4*)desc,
                      max_extra, degrid_direct(K, g.T, sizeof(R)),
                      (const cplx<R>*)planes, (const Record<R>*)records,
