@@ -615,12 +615,16 @@ __global__ __launch_bounds__(kTileWorkThreads) void k_tile_work(
 constexpr int kPartThreads = 1024;
 // Limits of the direct sort: keys (LDS words of its histogram), and
 // visibilities (beyond, its scattered record writes cost more than the
-// partition's second level).  The key totals come from one workgroup up to
-// kDirectCols histogram words (twelve rounds of loads), else from a kernel
-// of their own.
+// partition's second level).  Up to kDirectCols histogram words the key
+// totals come from the one workgroup of direct_tiles, a thread a key and
+// sixteen blocks a round of loads, else from a kernel of their own.  The sort
+// in us, that workgroup / the kernel (keys x blocks): 9 x 245 39.6 / 41.2,
+// 1152 x 4 18.2 / 19.6, 1008 x 16 17.9 / 18.3, 16128 x 1 41.9 / 42.8; 1152 x
+// 15 23.3 / 21.6, 9216 x 2 29.0 / 27.7, 9216 x 7 40.9 / 29.7, 16128 x 4 53.9 /
+// 43.2, 1008 x 65 35.0 / 32.7.
 constexpr int64_t kDirectKeys = 16384;
 constexpr int64_t kDirectVis = 1 << 20;
-constexpr uint64_t kDirectCols = 65536;
+constexpr uint64_t kDirectCols = 16384;
 constexpr int kPartSegs = 64;  // block segments of the level-1 scan
 
 // In-place exclusive scan of n LDS counters (each thread a contiguous run);

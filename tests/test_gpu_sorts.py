@@ -1,0 +1,75 @@
+"""The three ways to sort visibilities against each other where their inner
+launches change: tile statistics, dropped taps, images and degridded values of
+the automatic choice and the two-level partition against the hashed counting
+sort, which shares no offset code with either.
+
+Tolerances as in the other parity tests: FP64 rel-max 1e-12, FP32 rel-L2
+1e-5; counts exactly.
+"""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+
+import synth  # noqa: E402
+import paper_2301_06061_amd as ws  # noqa: E402
+
+pytestmark = pytest.mark.gpu
+
+# (n, nv, nw, m).  Direct sort: the key totals in the tile work workgroup up
+# to 16384 histogram words, else in a kernel of their own.  Partition: one
+# workgroup for the level-1 scan up to 65536 words, with several segments a
+# bucket, one (more than 512 buckets) and several turns a thread (more than
+# 1024).
+SIZES = [
+    (256, 256, 8, 14_336),      # 1152 keys x 14 blocks = 16128 words
+    (256, 256, 8, 14_337),      # 15 blocks: 17280
+    (512, 512, 16, 4_096),      # 9216 x 1
+    (512, 512, 16, 4_097),      # 9216 x 2
+    (512, 512, 28, 4_096),      # 16128 x 1
+    (512, 512, 28, 4_097),      # 16128 x 2
+    (64, 64, 1, 100_000),       # 9 keys
+    (512, 512, 29, 9_000),      # partition: 232 buckets
+    (512, 1024, 40, 300_000),   # 640 buckets, one segment
+    (512, 1024, 64, 300_000),   # 1024 x 74: four kernels
+    (256, 1024, 96, 20_000),    # 1536 buckets, two turns a thread
+    (256, 1024, 130, 50_000),   # 2080 buckets, three turns
+    (16, 2048, 33, 130_000),    # 4224 buckets x 32 (FP32): four kernels
+]
+
+
+def _err(a, b, fp64):
+    a, b = a.to(torch.complex128), b.to(torch.complex128)
+    if fp64:
+        return float((a - b).abs().max() / b.abs().max())
+    return float(torch.linalg.vector_norm(a - b) /
+                 torch.linalg.vector_norm(b))
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("n,nv,nw,m", SIZES)
+def test_sorts_agree(n, nv, nw, m, precision):
+    fp64 = precision == "fp64"
+    tol = 1e-12 if fp64 else 1e-5
+    wl = synth.edge_case(13, n=n, nv=nv, nw=nw,
+                         support=5 if min(n, nv) < 32 else 7, m=m,
+                         fov_deg=2.0 if nv <= 4 * n else 0.1,
+                         precision=1 if fp64 else 0)
+    uvw, vis, wt = (torch.from_numpy(np.ascontiguousarray(a)).cuda()
+                    for a in (wl.uvw, wl.vis, wl.weight))
+    x = torch.from_numpy(np.random.default_rng(2).standard_normal(
+        (nv, n))).cuda()
+    out = {}
+    for mode in ("hashed", "partition", "auto"):
+        plan = ws.WStackPlan.from_workload(wl, binning=mode)
+        drop = torch.zeros(1, dtype=torch.int64, device="cuda")
+        img = plan.dirty_image(uvw, vis, wt, dropped=drop)
+        out[mode] = (plan.tile_stats(), int(drop.item()), img,
+                     plan.degrid(x.to(plan.rdtype), uvw, wt))
+        plan.close()
+    ref = out.pop("hashed")
+    assert ref[0]["busy"] > 0 and bool((ref[2] != 0).any())
+    for mode, got in out.items():
+        assert got[0] == ref[0] and got[1] == ref[1], mode
+        assert _err(got[2], ref[2], fp64) <= tol, mode
+        assert _err(got[3], ref[3], fp64) <= tol, mode
