@@ -561,7 +561,6 @@ ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
     w.hist2x = pl->w<uint32_t>(L.o_p_hist2x);
     w.bounds = pl->w<uint32_t>(L.o_p_bounds);
     w.seg = pl->w<uint32_t>(L.o_p_seg);
-    w.sums = sums;
     w.rec1 = pl->work + L.o_p_rec1;
     w.keys = pl->w<uint32_t>(L.o_p_keys);
     w.chunk0 = pl->w<uint32_t>(L.o_p_chunk0);
@@ -618,11 +617,8 @@ GridJob<R> make_job(ws_plan* pl, int accumulate, bool ts = false) {
   GridJob<R> j;
   j.g = pl->g;
   j.pitch = grid_lds_pitch(L.T, pl->p.support);
-  j.offsets = pl->w<uint32_t>(L.o_counts);
   j.counters = pl->w<uint32_t>(L.o_counters);
-  j.busy = pl->w<uint32_t>(L.o_busy);
   j.idle = pl->w<uint32_t>(L.o_idle);
-  j.tile_chunks = pl->w<uint32_t>(L.o_chunks);
   j.tile_slot = pl->w<uint32_t>(L.o_slot);
   j.rec = pl->w<Record<R>>(L.o_rec);
   j.desc = pl->w<uint32_t>(L.o_desc);
@@ -631,7 +627,6 @@ GridJob<R> make_job(ws_plan* pl, int accumulate, bool ts = false) {
   j.accumulate = accumulate;
   j.zero_idle = lazy_ok(pl) ? 0 : 1;
   j.tstore = ts ? pl->w<cplx<R>>(L.o_tstore) : nullptr;
-  j.tslot = ts ? pl->w<uint32_t>(L.o_tslot) : nullptr;
   j.tcap = ts ? (uint32_t)L.tstore_slots : 0u;
   return j;
 }

@@ -2,7 +2,8 @@
 // w-screen kernels (Eq. 2, outer integral).
 //
 // Each 1-D transform is a Stockham autosort FFT (radix 8, one radix-4 or
-// radix-2 stage last) held in LDS: the first stage reads HBM directly and
+// radix-2 stage last; radix 16 first where a thread holds 16 points of a
+// long FP32 line) held in LDS: the first stage reads HBM directly and
 // the last writes HBM directly, so a transform costs one read and one write
 // of its line.  Rows are transformed one per workgroup; columns in blocks of
 // BC adjacent columns per workgroup (BC * 8 or 16 bytes per row segment),
@@ -17,9 +18,9 @@
 // F_k[q][p] exp(2 pi i w_k (n_pq - 1)) in registers, so the transformed
 // planes are never written back; the degridding counterpart multiplies an
 // image row by each plane's conjugate screen before transforming it.  The
-// screen phasor is advanced plane to plane by an FP64 complex multiply
-// (the planes are equispaced in w), seeded with FP64 sincospi of the
-// phase reduced to [-1/2, 1/2] turn.
+// planes are equispaced in w: a step from plane to plane and the phasor of
+// the first one come from FP64 sincospi of phases reduced to [-1/2, 1/2]
+// turn, and are applied in the path's precision.
 #include "ws_kernels.h"
 
 namespace ws {
@@ -1160,7 +1161,8 @@ __global__ __launch_bounds__(256) void k_wcorrect(const cplx<R>* __restrict__ F,
 //          one stage less).
 //   GMAX   lines (planes of one row) a workgroup, where the image has too few
 //          rows to fill the device
-//   TABLE  stage twiddles in a table; beyond 4096 points lookup tables
+//   TABLE  stage twiddles held whole (RowTwiddles); beyond 4096 points lookup
+//          tables
 //   FITS   the kernels exist: a line and the tables in one workgroup's LDS,
 //          and 16 wavefronts of registers
 //   SUMS   the summing kernel too: its accumulators and steps spill at 1024
@@ -1713,8 +1715,11 @@ bool cols4_t(cplx<R>* data, int ncols, int nplanes, const cplx<R>* tw, R s,
   }
 }
 
-// Wavefronts a launch should have at least, to keep every SIMD of the device
-// (256 CUs of four) busy with a few.
+// Wavefronts a launch should have at least: what FP32 kernels of 128 registers
+// fill the device's 1024 SIMDs with.  Row sums at 1024 / 2048 / 4096 / 8192, us:
+// 1024^2 x 16 FP32 50 / 50 / 41 / 43, 512^2 x 8 FP64 18.0 / 16.7 / 18.7 / 18.7,
+// 128^2 x 4 and 2048^2 x 16 the same; broadcast of 256^2 x 8 FP64 17.7 / 19.7 /
+// 19.5 / 20.0.
 constexpr int64_t kEnoughWaves = 4096;
 
 template <typename R, int LOGN, int G>

@@ -6,11 +6,10 @@
 // this part LDS FP64 atomic adds run about 20x faster than FP32 ones
 // (measured, 6.6 vs 0.33 lanes per clock per CU), so the FP32 path computes
 // its taps in FP32 and sums them in FP64 before rounding the finished tile
-// to FP32.  A wavefront takes one visibility at a time and its lanes cover
-// the K x K kernel taps, so the adds of one LDS instruction hit distinct
-// cells (no same-address serialisation, even in a dense core where many
-// visibilities share a cell); the LDS row pitch is T + K (odd), so they
-// also fall in distinct banks.
+// to FP32.  A wavefront takes floor(64 / K) visibilities at a time, K lanes
+// each, one kernel row a lane: every lane adds its row's K taps in turn, so
+// that the lanes of one visibility hit distinct cells in each LDS
+// instruction, and, the row pitch being odd, distinct banks.
 //
 // Latency hiding: the records of a tile come from up to ten key ranges
 // (its own bins and its neighbours' edge strips); they are read as one
@@ -24,8 +23,8 @@
 // tiles with more records than one chunk are split over several items
 // whose partial tiles a merge kernel sums in a fixed order.  The queue
 // hands out the extra chunks of split (hot) tiles first, then one item per
-// tile with records, then groups of tiles without records, which only get
-// zeros.
+// tile with records; tiles without records are zeroed by a kernel of their
+// own, or not at all.
 //
 // Degridding: one workgroup per (tile, chunk) item; tiles of a few records
 // are read from the transformed plane directly, denser ones staged in LDS with
@@ -632,7 +631,9 @@ __global__ __launch_bounds__(256) void k_zero_idle_batch(
 // kMergeLong chunks it takes kMergeCells cells instead and cuts their lists
 // into kMergeRuns runs, whose sums are added in order (1e6 visibilities on
 // 1024^2 x 16 planes in chunks of 512: 82 -> 70 us; runs for every tile cost
-// the 4096^2 x 32 case 8 us of idle threads).  The grid is at most
+// the 4096^2 x 32 case 8 us of idle threads).  kMergeLong of 4, 16, 64 and no
+// runs, us: 1024^2 x 16, 1e6 25.3 / 25.3 / 33.5 / 33.6, 4096^2 x 32, 1e7 50 /
+// 48 / 66 / 64, 512^2 x 8 FP64, 2e5 14.6 / 13.9 / 13.7 / 13.7.  The grid is at most
 // kMergeTiles tiles wide and strides over the split list, whose length only
 // the device knows: one workgroup for every scratch slot spent 10 us on
 // those that found nothing to do.

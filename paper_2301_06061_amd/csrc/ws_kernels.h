@@ -58,7 +58,6 @@ struct PartWork {
   uint32_t* btot;      // [blocks] records each workgroup placed
   uint32_t* bounds;    // [nbuckets + 1] first record of every bucket
   uint32_t* seg;       // [64][nbuckets] segment sums of the level-1 scan
-  uint32_t* sums;      // scan scratch
   void* rec1;          // [max_vis] records in bucket order
   uint32_t* keys;      // [max_vis] their keys
   uint32_t* chunk0;    // [nbuckets + 1] first level-2 chunk of each bucket
@@ -170,12 +169,9 @@ template <typename R>
 struct GridJob {
   Geo g;
   int pitch;                  // LDS row pitch of the tile (FP64 words)
-  const uint32_t* offsets;    // record offset of every key (+ total)
   uint32_t* counters;         // [1] split tiles, [2] extra items, [3] queue,
                               // [4] busy tiles, [5] idle tiles
-  const uint32_t* busy;       // tiles with records ([4] of them)
   const uint32_t* idle;       // tiles without ([5]), zeroed separately
-  const uint32_t* tile_chunks;
   const uint32_t* tile_slot;
   const Record<R>* rec;
   const uint32_t* desc;       // item descriptors (TileWork::desc)
@@ -184,11 +180,10 @@ struct GridJob {
   int accumulate;
   int zero_idle;              // batch: this job's idle tiles need zeros
   // Busy-tile store (one-call path of 4096-row FP32 stacks): finished
-  // tiles go to tstore[tslot[tile]] in column sub-blocks (tile_store_at)
-  // instead of the stack; null = the stack.  Tiles whose busy-list index
-  // (= slot) is tcap or more do not fit and go to the stack.
+  // tiles go to the slot of their busy-list index, in column sub-blocks
+  // (tile_store_at), instead of the stack; null = the stack.  Tiles whose
+  // index is tcap or more do not fit and go to the stack.
   cplx<R>* tstore;
-  const uint32_t* tslot;
   uint32_t tcap;
 };
 
