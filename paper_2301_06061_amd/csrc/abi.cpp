@@ -201,7 +201,7 @@ size_t partial_budget(const Layout& L) {
   return std::max((size_t)128 << 20, L.planes_bytes / 16);
 }
 
-// How make_layout sizes a plan.
+// How layout_of sizes a plan.
 struct Sizing {
   uint32_t chunk_at_least = 0;     // automatic chunks (raised up to 4096)
   int64_t max_slots = kMaxSlots;   // partial-tile slots
@@ -211,10 +211,9 @@ struct Sizing {
   bool admission = false;
 };
 
-ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
-                      const Sizing& z = Sizing()) {
-  ws_status st = check_params(p);
-  if (st != WS_OK) return st;
+// Sizes of a parameter set that check_params() has passed.
+ws_status layout_of(const ws_params* p, int64_t max_vis, Layout* L,
+                    const Sizing& z) {
   if (max_vis < 1 || max_vis > kMaxVis)
     return fail(WS_INVALID_ARG, "max_vis=%lld: need 1 <= max_vis < 2^31",
                 (long long)max_vis);
@@ -357,6 +356,11 @@ ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L,
   L->o_zero = take(256);
   L->total = o;
   return WS_OK;
+}
+
+ws_status make_layout(const ws_params* p, int64_t max_vis, Layout* L) {
+  const ws_status st = check_params(p);
+  return st == WS_OK ? layout_of(p, max_vis, L, Sizing()) : st;
 }
 
 }  // namespace
@@ -1312,7 +1316,9 @@ ws_status ws_grid_image_noalloc(const ws_params* params, int64_t m,
   Layout L;
   Sizing z;
   z.admission = true;
-  WS_TRY(make_layout(params, mv, &L, z));
+  // (Once: with the grid correction the checks take 2 ms of the host.)
+  WS_TRY(check_params(params));
+  WS_TRY(layout_of(params, mv, &L, z));
   const size_t planes_at = 0;
   const size_t work_at = align_up(L.planes_bytes, 256);
   const size_t need = work_at + L.total;
@@ -1328,17 +1334,17 @@ ws_status ws_grid_image_noalloc(const ws_params* params, int64_t m,
   // is one work item: 1e5 visibilities in one tile of 1024^2 x 6 planes take
   // 1420 us with 181 slots for items of 512 records, 130 us in items of 2048.
   z.admission = false;
-  WS_TRY(make_layout(params, mv, &L, z));
+  WS_TRY(layout_of(params, mv, &L, z));
   while (work_at + L.total > kNoAllocBytes && params->chunk == 0 &&
          L.chunk < 4096) {
     z.chunk_at_least = 2 * L.chunk;
-    WS_TRY(make_layout(params, mv, &L, z));
+    WS_TRY(layout_of(params, mv, &L, z));
   }
   if (work_at + L.total > kNoAllocBytes) {
     const size_t drop =
         (work_at + L.total - kNoAllocBytes + 255) / partial_bytes(L) + 1;
     z.max_slots = drop < L.max_slots ? (int64_t)(L.max_slots - drop) : 1;
-    WS_TRY(make_layout(params, mv, &L, z));
+    WS_TRY(layout_of(params, mv, &L, z));
   }
   if (work_at + L.total > kNoAllocBytes)
     return fail(WS_WORKSPACE_TOO_SMALL, "the static scratch is too small");

@@ -98,3 +98,27 @@ def test_dense_tile_near_the_limit(precision, nw, m):
         assert float(torch.linalg.vector_norm(d) /
                      torch.linalg.vector_norm(r)) <= 1e-5
     assert t_got <= 3.0 * t_ref, (t_got, t_ref)
+
+
+@pytest.mark.parametrize("m", [13, 30_000, 320_000])
+def test_parameters_are_checked_once(m):
+    """The checks of a plan with grid correction evaluate the kernel's
+    transform a few hundred times, milliseconds of the host: the call does
+    it once, also where it looks for a layout that fits."""
+    import time
+    p = _params(256, 256, 3, precision="fp64", kernel="es", correct=True)
+
+    def best(f):
+        times = []
+        for _ in range(15):
+            t = time.perf_counter()
+            f()
+            times.append(time.perf_counter() - t)
+        return min(times)
+
+    lib = _abi.lib()
+    call = best(lambda: lib.ws_grid_image_noalloc(
+        C.byref(p), m, None, None, None, None, None, None))
+    check = best(lambda: lib.ws_validate_params(C.byref(p)))
+    assert check > 1e-4
+    assert call <= 1.5 * check, (call, check)
