@@ -857,8 +857,11 @@ __global__ __launch_bounds__(kPartThreads) void k_part_bounds(
 // workgroup, for histograms of at most kSmallScan words: four launches of a
 // few microseconds each become one (28 -> 13 us for 244 workgroups of 256
 // buckets).  Thread (segment, bucket) sums its run of blocks eight loads at
-// a time; more than 1024 buckets take one segment and several turns.
+// a time; more than 1024 buckets take one segment and several turns.  At most
+// kSmallSegs segments, which one thread a bucket adds up in turn (with a
+// thread for every segment that fits, 1024 of them for one bucket, 27 us).
 constexpr uint32_t kSmallScan = 65536;
+constexpr uint32_t kSmallSegs = 32;
 
 __global__ __launch_bounds__(kPartThreads) void k_part_scan1_small(
     uint32_t* __restrict__ hist, uint32_t nb, uint32_t nc, uint32_t chunk,
@@ -868,7 +871,8 @@ __global__ __launch_bounds__(kPartThreads) void k_part_scan1_small(
   uint32_t* s_seg = s_bkt + nc;
   __shared__ uint32_t s_tmp[kPartThreads / 64];
   bin_clear(clear);
-  const uint32_t nseg = nc >= kPartThreads ? 1u : kPartThreads / nc;
+  const uint32_t nseg =
+      nc >= kPartThreads ? 1u : min(kPartThreads / nc, kSmallSegs);
   const uint32_t seg = threadIdx.x / nc, c0 = threadIdx.x % nc;
   const bool on = nc >= kPartThreads || seg < nseg;
   const uint32_t first = nc >= kPartThreads ? threadIdx.x : c0;

@@ -73,3 +73,29 @@ def test_sorts_agree(n, nv, nw, m, precision):
         assert got[0] == ref[0] and got[1] == ref[1], mode
         assert _err(got[2], ref[2], fp64) <= tol, mode
         assert _err(got[3], ref[3], fp64) <= tol, mode
+
+
+def test_scan_of_one_bucket_is_no_slower_than_of_many():
+    """The partition's level-1 scan over 269 blocks of one bucket against 8
+    buckets (the smallest time of eight): at most 1.8 times."""
+    us = []
+    for n, nw in ((64, 1), (128, 4)):
+        m, fov = 1_100_000, 0.03
+        g = torch.Generator(device="cuda")
+        g.manual_seed(1)
+        f64 = dict(generator=g, device="cuda", dtype=torch.float64)
+        uvw = torch.cat([(torch.rand(m, 2, **f64) - 0.5) * (n - 10) / fov,
+                         torch.rand(m, 1, **f64) * 2 - 1], 1).contiguous()
+        vis = torch.ones(m, dtype=torch.complex64, device="cuda")
+        plan = ws.WStackPlan(n, n, nw, fov, fov, -1.0, 1.0, 7, max_vis=m,
+                             binning="partition")
+        plan.dirty_image(uvw, vis)
+        best = []
+        for _ in range(8):
+            plan.set_profiling(True)
+            plan.dirty_image(uvw, vis)
+            best.append(plan.kernel_times(True)["part_scan1"][0] * 1e3)
+            plan.set_profiling(False)
+        us.append(min(best))
+        plan.close()
+    assert us[0] <= 1.8 * us[1], us
