@@ -96,9 +96,9 @@ typedef int32_t ws_status;
  *            0 = automatic
  *   chunk    most visibilities one gridding work item accumulates before a
  *            split tile is merged; 0 = automatic: the least power of two c
- *            from 512 to 4096 with c^2 >= max_vis whose partial tiles of
- *            split tiles (2 max_vis / c + 64, at most 4096, 64 KB each for
- *            tile edge 64) take at most 128 MiB or a sixteenth of the plane
+ *            from 512 to 4096 with c^2 >= max_vis whose scratch for
+ *            split tiles takes at most 4096 partial tiles (64 KB each for
+ *            tile edge 64) and at most 160 MiB or a sixteenth of the plane
  *            stack.  In a batch, items are at least as large as all its
  *            plans' max_vis together give by the first rule: a program that
  *            knows its batch saves workspace by asking for that chunk

@@ -49,6 +49,9 @@ class BatchedImager:
         self.plans: List[WStackPlan] = []
         self.tuned = []
         counts = [max(1, int(u.shape[0])) for u in self.uvw]
+        # Workspaces for the batch's items, where they are the largest, not
+        # for the smaller ones of a plan by itself.
+        whole = 4096 if batch_chunk(counts) == 4096 else 0
         with torch.cuda.stream(self.stream):
             for i, wl in enumerate(workloads):
                 tile, chunk = 0, 0
@@ -63,10 +66,7 @@ class BatchedImager:
                                wl.w_min, wl.w_max, wl.support,
                                getattr(wl, "sigma", 0.0), precision,
                                max_vis=counts[i], tile=tile,
-                               # Workspaces for the batch's items, not for
-                               # the smaller ones of a plan by itself.
-                               chunk=chunk or batch_chunk(counts),
-                               device=self.device,
+                               chunk=chunk or whole, device=self.device,
                                kernel=getattr(wl, "kernel", "gauss"),
                                beta=getattr(wl, "beta", 0.0),
                                correct=bool(getattr(wl, "correct", False)))

@@ -182,11 +182,20 @@ uint32_t auto_chunk(int64_t max_vis) {
 
 // Scratch slots for the partial tiles of split tiles, and the bytes of one.
 // A tile that finds too few left becomes one work item, however many records
-// it has, so the slots are sized for twice the visibilities (a dense core
-// on a corner of four tiles reads each up to two times on average).
+// it has, so the slots hold twice the visibilities and 2^18 records more,
+// with automatic items of any size, or what they can need at all if that is
+// less: every visibility read by four tiles, and a part of an item over on
+// each split tile.  (Dense cores lie on a corner of four tiles: a core of
+// 155 209 on 128^2 x 5 planes with K = 15 is read 3.1 times over.  2 max_vis /
+// 512 + 64 slots left tiles of 2e4 records whole: 975 us, these 167; items of
+// 4096 records 311.)  Items of a size that was asked for get 64 slots over.
 constexpr int64_t kMaxSlots = 4096;
-int64_t wanted_slots(int64_t max_vis, uint32_t chunk) {
-  return std::min(2 * max_vis / chunk + 64, kMaxSlots);
+int64_t wanted_slots(const ws_params* p, int64_t max_vis, const Layout& L) {
+  const int64_t twice = 2 * max_vis / L.chunk;
+  if (p->chunk != 0) return twice + 64;
+  const int64_t four = 4 * max_vis / L.chunk;
+  return std::max<int64_t>(1, std::min(twice + (1 << 18) / L.chunk,
+                                       four + std::min(four, L.ntiles)));
 }
 size_t partial_bytes(const Layout& L) {
   return (size_t)L.T * L.T * 2 *
@@ -194,11 +203,14 @@ size_t partial_bytes(const Layout& L) {
 }
 // Automatic items smaller than 4096 records cost slots: up to 4 KB of partial
 // tiles a visibility for edge-64 tiles (at 512 records; 0.5 KB at 4096).
-// They may take 128 MiB or a sixteenth of the plane stack together: 1e6
-// visibilities keep items of 1024 (2017 slots), 4e6 on less than 2 GB of
-// planes take 4096 instead of 2048 (a 512^2 x 4 image 629 us against 633).
-size_t partial_budget(const Layout& L) {
-  return std::max((size_t)128 << 20, L.planes_bytes / 16);
+// They may take 160 MiB or a sixteenth of the plane stack together, and
+// kMaxSlots: 1e6 visibilities keep items of 1024 (a 1024^2 x 16 image whose
+// core lies in few planes 329 us, in items of 2048 358), 4e6 on 512^2 x 4 take
+// 4096 instead of 2048 (629 us against 633).
+bool slots_fit(const Layout& L, int64_t slots) {
+  return slots <= kMaxSlots &&
+         slots * partial_bytes(L) <=
+             std::max((size_t)160 << 20, L.planes_bytes / 16);
 }
 
 // How layout_of sizes a plan.
@@ -227,12 +239,11 @@ ws_status layout_of(const ws_params* p, int64_t max_vis, Layout* L,
   L->chunk = p->chunk != 0  ? (uint32_t)p->chunk
              : z.admission ? 4096u
                            : std::max(auto_chunk(max_vis), z.chunk_at_least);
-  while (p->chunk == 0 && L->chunk < 4096 &&
-         wanted_slots(max_vis, L->chunk) * partial_bytes(*L) >
-             partial_budget(*L))
-    L->chunk *= 2;
   const int64_t tu = p->nu / L->T, tv = p->nv / L->T;
   L->ntiles = tu * tv * p->nw;
+  while (p->chunk == 0 && L->chunk < 4096 &&
+         !slots_fit(*L, wanted_slots(p, max_vis, *L)))
+    L->chunk *= 2;
   L->nkeys = L->ntiles * kRegions;
   if (L->nkeys >= (int64_t)0xFFFFFFF0ll)
     return fail(WS_UNSUPPORTED_SIZE, "too many bins (%lld)",
@@ -259,7 +270,9 @@ ws_status layout_of(const ws_params* p, int64_t max_vis, Layout* L,
     L->direct = !z.admission && p->binning == WS_BINNING_AUTO &&
                 direct_fits(max_vis, L->nkeys);
   }
-  const int64_t slots = std::min(wanted_slots(max_vis, L->chunk), z.max_slots);
+  const int64_t want = z.admission ? 2 * max_vis / L->chunk + 64
+                                   : wanted_slots(p, max_vis, *L);
+  const int64_t slots = std::min({want, kMaxSlots, z.max_slots});
   L->max_slots = (uint32_t)slots;
   // Further work items beyond one per tile: at most max_slots when
   // gridding (split tiles hold scratch slots), at most max_vis / chunk when
@@ -537,9 +550,10 @@ ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
   tw.strips = strips;
   tw.tslot = tslot;
   tw.desc = pl->w<uint32_t>(L.o_desc);
-  // Items: one per tile plus the further chunks of split tiles.
-  const int64_t reads = degrid ? m : 4 * m;
-  int64_t extra = (reads + chunk - 1) / chunk + 1;
+  // Items: one per tile plus the further chunks of split tiles.  Degridding
+  // launches a block for each; gridding sizes its persistent launch by them,
+  // where a generous bound only adds workgroups that find nothing to do.
+  int64_t extra = degrid ? (m + chunk - 1) / chunk + 1 : 2 * m / chunk + 64;
   if (extra > L.max_extra) extra = L.max_extra;
   *max_items = (uint32_t)(L.ntiles + extra);
   if (L.direct) {
@@ -643,7 +657,9 @@ ws_status merge_impl(ws_plan* pl, int acc, bool ts = false) {
                          pl->w<uint32_t>(L.o_split),
                          pl->w<uint32_t>(L.o_chunks),
                          pl->w<uint32_t>(L.o_slot), pl->work + L.o_partials,
-                         pl->planes, acc, L.max_slots / 2 + 1,
+                         pl->planes, acc,
+                         (uint32_t)std::min<int64_t>(L.max_slots / 2 + 1,
+                                                     L.ntiles),
                          ts ? pl->work + L.o_tstore : nullptr,
                          ts ? pl->w<uint32_t>(L.o_tslot) : nullptr,
                          (uint32_t)L.tstore_slots, pl->stream);
