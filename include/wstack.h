@@ -347,8 +347,8 @@ ws_status ws_clean_minor(ws_plan* plan, void* residual, const void* beam,
  * 85 bytes (FP32) or 135 (FP64) a visibility, and 64 tiles.  It is not what
  * ws_workspace_bytes reports: a plan sorts small problems in one level, and
  * makes smaller items with more and FP64 partial tiles.  This call does the
- * same as far as the scratch allows and otherwise makes its items larger (up
- * to 4096 records), then keeps fewer partial tiles.  Every call
+ * same as far as the scratch allows and otherwise makes its items larger and
+ * keeps fewer partial tiles.  Every call
  * on one GPU shares that GPU's scratch: calls that overlap in time on one
  * GPU (two streams, two threads) race and give wrong images; serialise
  * them.  The scratch keeps the last call's contents; each call clears what

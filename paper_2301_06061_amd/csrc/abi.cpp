@@ -181,18 +181,20 @@ uint32_t auto_chunk(int64_t max_vis) {
 }
 
 // Scratch slots for the partial tiles of split tiles, and the bytes of one.
-// A tile that finds too few left becomes one work item, however many records
-// it has, so the slots hold twice the visibilities and 2^18 records more,
-// with automatic items of any size, or what they can need at all if that is
-// less: every visibility read by four tiles, and a part of an item over on
-// each split tile.  (Dense cores lie on a corner of four tiles: a core of
-// 155 209 on 128^2 x 5 planes with K = 15 is read 3.1 times over.  2 max_vis /
-// 512 + 64 slots left tiles of 2e4 records whole: 975 us, these 167; items of
-// 4096 records 311.)  Items of a size that was asked for get 64 slots over.
+// Dense cores lie on a corner of four tiles: one of 155 209 visibilities on
+// 128^2 x 5 planes with K = 15 is read 3.1 times over.  Where slots run out the
+// direct sort starts over with larger items, and twice the visibilities and
+// 64 slots do (that image: 191 us; items of 4096 records 311; where the
+// tiles left over became one item each, however dense, 975).  The tile work
+// pass of the other sorts cannot start over and makes those items: their
+// slots hold twice the visibilities and 2^18 records more, with automatic
+// items of any size, or what they can need at all if that is less: every
+// visibility read by four tiles, and a part of an item over on each split
+// tile.  Items of a size that was asked for get 64 slots over.
 constexpr int64_t kMaxSlots = 4096;
 int64_t wanted_slots(const ws_params* p, int64_t max_vis, const Layout& L) {
   const int64_t twice = 2 * max_vis / L.chunk;
-  if (p->chunk != 0) return twice + 64;
+  if (p->chunk != 0 || L.direct) return twice + 64;
   const int64_t four = 4 * max_vis / L.chunk;
   return std::max<int64_t>(1, std::min(twice + (1 << 18) / L.chunk,
                                        four + std::min(four, L.ntiles)));
@@ -241,9 +243,6 @@ ws_status layout_of(const ws_params* p, int64_t max_vis, Layout* L,
                            : std::max(auto_chunk(max_vis), z.chunk_at_least);
   const int64_t tu = p->nu / L->T, tv = p->nv / L->T;
   L->ntiles = tu * tv * p->nw;
-  while (p->chunk == 0 && L->chunk < 4096 &&
-         !slots_fit(*L, wanted_slots(p, max_vis, *L)))
-    L->chunk *= 2;
   L->nkeys = L->ntiles * kRegions;
   if (L->nkeys >= (int64_t)0xFFFFFFF0ll)
     return fail(WS_UNSUPPORTED_SIZE, "too many bins (%lld)",
@@ -270,6 +269,9 @@ ws_status layout_of(const ws_params* p, int64_t max_vis, Layout* L,
     L->direct = !z.admission && p->binning == WS_BINNING_AUTO &&
                 direct_fits(max_vis, L->nkeys);
   }
+  while (p->chunk == 0 && L->chunk < 4096 &&
+         !slots_fit(*L, wanted_slots(p, max_vis, *L)))
+    L->chunk *= 2;
   const int64_t want = z.admission ? 2 * max_vis / L->chunk + 64
                                    : wanted_slots(p, max_vis, *L);
   const int64_t slots = std::min({want, kMaxSlots, z.max_slots});
@@ -1344,15 +1346,15 @@ ws_status ws_grid_image_noalloc(const ws_params* params, int64_t m,
                 "allocation-free call has a %zu-byte static scratch (use "
                 "ws_grid_init with caller buffers instead)",
                 need, kNoAllocBytes);
-  // Near the limit the partial-tile slots get what is left: first larger
-  // items, which need fewer, then, at 4096 records, as many slots as there is
-  // room for (half of the admission size's at least).  A tile without slots
-  // is one work item: 1e5 visibilities in one tile of 1024^2 x 6 planes take
-  // 1420 us with 181 slots for items of 512 records, 130 us in items of 2048.
+  // Near the limit the partial-tile slots get what is left (half of the
+  // admission size's at least).  The direct sort makes larger items itself
+  // where they run out; for the others larger items, which need fewer, come
+  // first.  (1e5 visibilities in one tile of 1024^2 x 6 planes took 1420 us
+  // with 181 slots for items of 512 records and one item for what was left.)
   z.admission = false;
   WS_TRY(layout_of(params, mv, &L, z));
   while (work_at + L.total > kNoAllocBytes && params->chunk == 0 &&
-         L.chunk < 4096) {
+         !L.direct && L.chunk < 4096) {
     z.chunk_at_least = 2 * L.chunk;
     WS_TRY(layout_of(params, mv, &L, z));
   }

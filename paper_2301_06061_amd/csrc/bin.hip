@@ -469,27 +469,24 @@ __device__ __forceinline__ TileDesc tile_desc(const TileWork& w, int t,
 }
 
 // Descriptor of chunk c.
+template <bool DEGRID>
 __device__ __forceinline__ void put_desc(const Geo& g, const TileWork& w,
                                          const TileDesc& d, uint32_t c) {
   const size_t n = c == 0 ? (size_t)d.at : (size_t)g.ntiles + d.e0 + c - 1;
   uint4* p = reinterpret_cast<uint4*>(w.desc);
-  if (w.degrid) {
+  if constexpr (DEGRID) {
     const uint32_t b = d.first + c * w.chunk, end = d.first + d.work;
     p[n] = make_uint4(d.tile, b, d.nch == 1 ? end : min(end, b + w.chunk), 0u);
-    return;
+  } else {
+    p += n * (kDescWords / 4);
+    p[0] = make_uint4(d.tile, d.nch, d.nch == 1 ? d.at : c, c * w.chunk);
+    p[1] = make_uint4(d.nch == 1 ? d.work : min(d.work, (c + 1) * w.chunk),
+                      d.ranges[0], d.ranges[1], d.ranges[2]);
+#pragma unroll
+    for (int q = 2; q < kDescWords / 4; ++q)
+      p[q] = make_uint4(d.ranges[4 * q - 5], d.ranges[4 * q - 4],
+                        d.ranges[4 * q - 3], d.ranges[4 * q - 2]);
   }
-  uint32_t o[kDescWords];
-  o[0] = d.tile;
-  o[1] = d.nch;
-  o[2] = d.nch == 1 ? d.at : c;
-  o[3] = c * w.chunk;
-  o[4] = d.nch == 1 ? d.work : min(d.work, (c + 1) * w.chunk);
-#pragma unroll
-  for (int q = 5; q < kDescWords; ++q) o[q] = d.ranges[q - 5];
-  p += n * (kDescWords / 4);
-#pragma unroll
-  for (int q = 0; q < kDescWords / 4; ++q)
-    p[q] = make_uint4(o[4 * q], o[4 * q + 1], o[4 * q + 2], o[4 * q + 3]);
 }
 
 // Descriptors of the items of a wavefront's tiles (one a lane, nch = 0 for
@@ -500,10 +497,14 @@ __device__ __forceinline__ void put_desc(const Geo& g, const TileWork& w,
 // With 3, 6 and 16 of its own: 1024^2 x 16, 1e6 14.0 / 12.4 / 11.5, 128^2 x 4,
 // 2e4 (whole sort) 20.4 / 19.4 / 18.7.
 constexpr uint32_t kOwnDescs = 16;
-__device__ __forceinline__ void emit_descs(const Geo& g, const TileWork& w,
-                                           const TileDesc& d) {
+template <bool DEGRID>
+__device__ __forceinline__ void spread_descs(const Geo& g, const TileWork& w,
+                                             const TileDesc& d) {
   const bool own = d.nch <= kOwnDescs;
-  for (uint32_t c = 0; own && c < d.nch; ++c) put_desc(g, w, d, c);
+  if (own && d.nch != 0) {
+
+    for (uint32_t c = 0; c < d.nch; ++c) put_desc<DEGRID>(g, w, d, c);
+  }
   unsigned long long rest = __ballot(!own);
   while (rest != 0) {
     const int l = __ffsll((long long)rest) - 1;
@@ -518,11 +519,20 @@ __device__ __forceinline__ void emit_descs(const Geo& g, const TileWork& w,
     o.at = of(d.at);
     o.e0 = of(d.e0);
     o.first = of(d.first);
+    if constexpr (!DEGRID) {
 #pragma unroll
-    for (int q = 0; q < 2 * kSegments - 1; ++q) o.ranges[q] = of(d.ranges[q]);
+      for (int q = 0; q < 2 * kSegments - 1; ++q)
+        o.ranges[q] = of(d.ranges[q]);
+    }
     for (uint32_t c = threadIdx.x & 63u; c < o.nch; c += 64u)
-      put_desc(g, w, o, c);
+      put_desc<DEGRID>(g, w, o, c);
   }
+}
+
+__device__ __forceinline__ void emit_descs(const Geo& g, const TileWork& w,
+                                           const TileDesc& d) {
+  if (w.degrid) spread_descs<true>(g, w, d);
+  else spread_descs<false>(g, w, d);
 }
 
 // One thread per tile.  Same-address atomics are the cost of this kernel (11.5
@@ -1180,21 +1190,33 @@ __global__ __launch_bounds__(kPartThreads) void k_direct_tiles(
   __syncthreads();
   for (uint32_t c = threadIdx.x; c <= nkeys; c += kPartThreads)
     offsets[c] = s_off[c];
-  for (int t0 = 0; t0 < g.ntiles; t0 += kPartThreads) {
-    const int t = t0 + (int)threadIdx.x;
-    const bool live = t < g.ntiles;
-    TileRecords r;
-    r.work = 0;
-    if (live) r = tile_records(g, t, w.degrid, s_off);
-    const uint32_t ib = wave_append(&s_ctr[4], live && r.work > 0);
-    const uint32_t ii = wave_append(&s_ctr[5], live && r.work == 0);
-    if (r.work > 0) atomicAdd(&s_reads, (unsigned long long)r.work);
-    const uint32_t at = r.work > 0 ? ib : ii;
-    uint32_t nch = 0, e0 = 0;
-    if (live) nch = emit_tile(g, w, t, r.work, at, s_ctr, e0);
-    emit_descs(g, w, tile_desc(w, t, r, nch, at, e0));
+  for (;;) {
+    for (int t0 = 0; t0 < g.ntiles; t0 += kPartThreads) {
+      const int t = t0 + (int)threadIdx.x;
+      const bool live = t < g.ntiles;
+      TileRecords r;
+      r.work = 0;
+      if (live) r = tile_records(g, t, w.degrid, s_off);
+      const uint32_t ib = wave_append(&s_ctr[4], live && r.work > 0);
+      const uint32_t ii = wave_append(&s_ctr[5], live && r.work == 0);
+      if (r.work > 0) atomicAdd(&s_reads, (unsigned long long)r.work);
+      const uint32_t at = r.work > 0 ? ib : ii;
+      uint32_t nch = 0, e0 = 0;
+      if (live) nch = emit_tile(g, w, t, r.work, at, s_ctr, e0);
+      emit_descs(g, w, tile_desc(w, t, r, nch, at, e0));
+    }
+    __syncthreads();
+    // Scratch slots ran out (never in degridding, which takes none): all
+    // over again with larger items, rather than tiles of any size in one
+    // item.  Ends at the latest where an item holds the largest tile.
+    if (s_ctr[0] <= w.max_slots) break;
+    __threadfence();
+    __syncthreads();
+    if (threadIdx.x < 8) s_ctr[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) s_reads = 0ull;
+    w.chunk *= 2u;
+    __syncthreads();
   }
-  __syncthreads();
   if (threadIdx.x < 6) w.counters[threadIdx.x] = s_ctr[threadIdx.x];
   if (threadIdx.x == 6) w.counters[6] = (uint32_t)s_reads;
   if (threadIdx.x == 7) w.counters[7] = (uint32_t)(s_reads >> 32);

@@ -64,3 +64,41 @@ def test_no_slower_than_items_of_4096(n, nw, m, law, K, precision):
                 torch.linalg.vector_norm(ref))
     assert err <= (1e-13 if precision == "fp64" else 1e-6), err
     assert t <= 1.2 * t_ref, (t, t_ref)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp64"])
+@pytest.mark.parametrize("m,chunk", [(3_000, 16), (9_000, 16), (20_000, 7)])
+def test_slots_run_out(m, chunk, precision):
+    """All visibilities about the origin, each read by four tiles, in items
+    that would need four slots a chunk where two are reserved: the direct sort
+    takes larger items.  Image, slabs and statistics against the hashed sort
+    with items of 4096."""
+    n, nw, K = 128, 2, 7
+    uvw, vis = _inputs(n, m, "point", precision)
+    out = []
+    for binning, c in (("auto", chunk), ("hashed", 4096)):
+        plan = ws.WStackPlan(n, n, nw, 0.03, 0.03, -50.0, 50.0, K,
+                             precision=precision, max_vis=m, chunk=c,
+                             binning=binning)
+        drop = torch.zeros(1, dtype=torch.int64, device="cuda")
+        img = plan.dirty_image(uvw, vis, dropped=drop)
+        st = plan.tile_stats()
+        plan.reset()
+        plan.grid(uvw[:m // 3], vis[:m // 3])
+        plan.grid(uvw[m // 3:], vis[m // 3:])
+        two = plan.new_image()
+        plan.image_accumulate(two)
+        out.append((img, two, st, int(drop.item())))
+        plan.close()
+    a, b = out
+    tol = 1e-12 if precision == "fp64" else 1e-6
+    for x in (a[0], a[1]):
+        assert float(torch.linalg.vector_norm(x - b[0]) /
+                     torch.linalg.vector_norm(b[0])) <= tol
+    for key in ("busy", "idle", "strips", "record_reads"):
+        assert a[2][key] == b[2][key], key
+    assert a[3] == b[3]
+    # Every dense tile is split, into no more items than there are slots.
+    slots = 2 * m // chunk + 64
+    assert a[2]["split"] == 4 * nw
+    assert a[2]["extra_items"] + a[2]["split"] <= slots

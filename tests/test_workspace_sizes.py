@@ -23,11 +23,15 @@ def _bytes(n, nw, m, precision="fp32", **kw):
 def test_partial_tiles_stay_within_their_bound(n, nw, m, precision):
     planes, auto = _bytes(n, nw, m, precision)
 
-    # Slots of 64 KB: twice the visibilities and 2^18 records over, or all
-    # that four reads of each can need.
+    # Slots of 64 KB: twice the visibilities and 64 over (up to 16384 keys,
+    # nine a tile, and 2^20 visibilities); else 2^18 records over, or all that
+    # four reads of each can need.
+    tiles = (n // 64) ** 2 * nw
+
     def slots(c):
         four = 4 * m // c
-        tiles = (n // 64) ** 2 * nw
+        if 9 * tiles <= 16384 and m <= 2 ** 20:
+            return 2 * m // c + 64
         return max(1, min(2 * m // c + 2 ** 18 // c, four + min(four, tiles)))
 
     # The least power of two from 512 to 4096 that reaches the square root of
