@@ -96,7 +96,8 @@ typedef int32_t ws_status;
  *            0 = automatic
  *   chunk    most visibilities one gridding work item accumulates before a
  *            split tile is merged; 0 = automatic: the least power of two c
- *            from 512 to 4096 with c^2 >= max_vis whose scratch for
+ *            from 512 to 4096 with c min(support, 7) / 7 at least the
+ *            square root of max_vis and whose scratch for
  *            split tiles takes at most 4096 partial tiles (64 KB each for
  *            tile edge 64) and at most 160 MiB or a sixteenth of the plane
  *            stack.  In a batch, items are at least as large as all its

@@ -19,12 +19,13 @@ from . import _abi
 from .api import WStackPlan, _ptr
 
 
-def batch_chunk(max_vis: Sequence[int]) -> int:
+def batch_chunk(max_vis: Sequence[int], support: int) -> int:
     """Records per work item that ws_batch_image uses for plans with
-    automatic chunks: the least power of two c from 512 to 4096 whose square
-    reaches the visibilities of all plans together."""
+    automatic chunks: the least power of two c from 512 to 4096 with c
+    min(support, 7) / 7 at least the square root of the visibilities of all
+    plans together."""
     c = 512
-    while c < 4096 and c * c < sum(max_vis):
+    while c < 4096 and (c * min(support, 7)) ** 2 < 49 * sum(max_vis):
         c *= 2
     return c
 
@@ -51,7 +52,8 @@ class BatchedImager:
         counts = [max(1, int(u.shape[0])) for u in self.uvw]
         # Workspaces for the batch's items, where they are the largest, not
         # for the smaller ones of a plan by itself.
-        whole = 4096 if batch_chunk(counts) == 4096 else 0
+        whole = 4096 if batch_chunk(
+            counts, workloads[0].support) == 4096 else 0
         with torch.cuda.stream(self.stream):
             for i, wl in enumerate(workloads):
                 tile, chunk = 0, 0

@@ -166,17 +166,22 @@ ws_status check_params(const ws_params* p) {
   return WS_OK;
 }
 
-// Records one work item takes (automatic): the least power of two c in
-// [512, 4096] with c^2 >= max_vis.  An item is one workgroup, 512 run at
+// Records one work item takes (automatic): for K >= 7 the least power of two c
+// in [512, 4096] with c^2 >= max_vis.  An item is one workgroup, 512 run at
 // once, and the longest of them ends the launch: its time grows with c.  The
 // partial tiles of split tiles cost a write and a read each: their number
 // grows with max_vis / c.  Gridding and merge, us, at c = 512 / 1024 / 2048 /
 // 4096: 2e4 visibilities on 128^2 x 4 planes 29 / 33 / 44 / 67; 2e5 on
 // 512^2 x 8 FP64 74 / 84 / 100 / 125; 1e6 on 1024^2 x 16 215 / 163 / 169 /
-// 218; 1e7 on 4096^2 x 32 (2048, 4096) 1080 / 1000.
-uint32_t auto_chunk(int64_t max_vis) {
+// 218; 1e7 on 4096^2 x 32 (2048, 4096) 1080 / 1000.  That is for K = 7 and
+// more; a record of K < 7 takes its item less time, and c K / 7 takes the place
+// of c.  A whole image, us, at 512 / 1024 / 2048 / 4096: K = 1 on 256^2 x 6,
+// 132 328 74 / 69 / 54 / 51, 128^2 x 5 FP64, 155 209 74 / 65 / 58 / 59; K = 3 84
+// / 77 / 74 / 83; K = 5 97 / 86 / 93 / 104.
+uint32_t auto_chunk(int64_t max_vis, int K) {
+  const int64_t k = std::min(K, 7);
   uint32_t c = 512;
-  while (c < 4096 && (int64_t)c * c < max_vis) c *= 2;
+  while (c < 4096 && c * c * k * k < 49 * max_vis) c *= 2;
   return c;
 }
 
@@ -240,7 +245,8 @@ ws_status layout_of(const ws_params* p, int64_t max_vis, Layout* L,
   L->planes_bytes = (size_t)p->nw * p->nv * p->nu * L->elem;
   L->chunk = p->chunk != 0  ? (uint32_t)p->chunk
              : z.admission ? 4096u
-                           : std::max(auto_chunk(max_vis), z.chunk_at_least);
+                           : std::max(auto_chunk(max_vis, p->support),
+                                    z.chunk_at_least);
   const int64_t tu = p->nu / L->T, tv = p->nv / L->T;
   L->ntiles = tu * tv * p->nw;
   L->nkeys = L->ntiles * kRegions;
@@ -978,7 +984,7 @@ ws_status batch_image_impl(ws_batch* b, const int64_t* m,
   // follow the batch's visibilities, not each plan's.
   int64_t vis_total = 0;
   for (int i = 0; i < b->n; ++i) vis_total += b->plans[i]->max_vis;
-  const uint32_t chunk = auto_chunk(vis_total);
+  const uint32_t chunk = auto_chunk(vis_total, b->K);
   for (int i = 0; i < b->n; ++i) {
     ws_plan* pl = b->plans[i];
     pl->stream = b->stream;

@@ -12,7 +12,11 @@ import paper_2301_06061_amd as ws  # noqa: E402
 
 pytestmark = pytest.mark.gpu
 
-CASES = [(128, 5, 155_209, "core", 15, "fp64"),
+CASES = [(128, 5, 155_209, "core", 1, "fp64"),
+         (256, 6, 132_328, "uniform", 1, "fp32"),
+         (128, 5, 155_209, "core", 3, "fp64"),
+         (512, 8, 200_000, "core", 5, "fp64"),
+         (128, 5, 155_209, "core", 15, "fp64"),
          (128, 4, 60_000, "point", 7, "fp32"),
          (256, 8, 30_000, "point", 9, "fp32"),
          (512, 8, 200_000, "core", 15, "fp32"),
