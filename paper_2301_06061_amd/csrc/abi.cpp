@@ -560,8 +560,11 @@ ws_status bin_records(ws_plan* pl, int64_t m, const VisSource& src,
   tw.desc = pl->w<uint32_t>(L.o_desc);
   // Items: one per tile plus the further chunks of split tiles.  Degridding
   // launches a block for each; gridding sizes its persistent launch by them,
-  // where a generous bound only adds workgroups that find nothing to do.
-  int64_t extra = degrid ? (m + chunk - 1) / chunk + 1 : 2 * m / chunk + 64;
+  // and workgroups that find nothing to do cost it: 1587 visibilities on 128 x
+  // 256 x 8 planes 41.8 us an image, 42.8 with 64 further items.
+  const int64_t reads = degrid ? m : 4 * m;
+  int64_t extra = (reads + chunk - 1) / chunk + 1;
+  if (!degrid) extra = std::min(extra, 2 * m / chunk + 64);
   if (extra > L.max_extra) extra = L.max_extra;
   *max_items = (uint32_t)(L.ntiles + extra);
   if (L.direct) {
