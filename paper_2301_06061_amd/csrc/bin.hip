@@ -501,10 +501,8 @@ template <bool DEGRID>
 __device__ __forceinline__ void spread_descs(const Geo& g, const TileWork& w,
                                              const TileDesc& d) {
   const bool own = d.nch <= kOwnDescs;
-  if (own && d.nch != 0) {
-
+  if (own)
     for (uint32_t c = 0; c < d.nch; ++c) put_desc<DEGRID>(g, w, d, c);
-  }
   unsigned long long rest = __ballot(!own);
   while (rest != 0) {
     const int l = __ffsll((long long)rest) - 1;
